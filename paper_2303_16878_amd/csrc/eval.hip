@@ -500,23 +500,25 @@ __device__ __forceinline__ void load_stencil(V (&t)[12], L ld, int voff, int row
 
 // ADJ: the loss adjoint -- only b (gradient) is accumulated, and dF/d(image) is scattered into
 // the gradient arenas with hardware float atomics.
-// ZB: the z-buffer occlusion variant (a separate instantiation, so the plain evaluation carries
-// none of its code).
+// ZB: the z-buffer occlusion variant (separate instantiations, so the plain evaluation carries none of
+// its code): 0 off, 1 evaluation with the z-test, 2 the projection-only pass that fills the z-buffers
+// (one instantiation per model pair; its geometry is FP64 whatever the evaluation precision).
 // BF: intensity and normal planes stored as BF16 (a separate instantiation; FP32 path only).
-template <typename T, int NCH, int SM, int TM, int GM, bool DBG, bool ADJ = false, bool ZB = false, bool BF = false>
+template <typename T, int NCH, int SM, int TM, int GM, bool DBG, bool ADJ = false, int ZB = 0, bool BF = false>
 __global__ void __launch_bounds__(kBlock)
     // two cues between pinhole sensors (FP32): six waves per SIMD (80 VGPRs), which the register allocator
     // would otherwise miss by one
     __attribute__((amdgpu_waves_per_eu(
-        std::is_same<T, float>::value && !DBG && !ADJ && NCH == 2 && SM == MODEL_PINHOLE && TM == MODEL_PINHOLE ? 6
+        std::is_same<T, float>::value && !DBG && !ADJ && ZB != 2 && NCH == 2 && SM == MODEL_PINHOLE && TM == MODEL_PINHOLE ? 6
                                                                                                              : 1)))
     eval_kernel(EvalArgs a, int item_base, int n_items)
 {
-    __shared__ WaveQueue<T> s_q[kBlock / 64];
+    constexpr bool ZTEST = ZB == 1, ZPASS = ZB == 2;
+    __shared__ WaveQueue<T> s_q[ZPASS ? 1 : kBlock / 64];
     __shared__ WaveQueueA s_qa[kBlock / 64];
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave index: uniform
-    WaveQueue<T> &Q = s_q[wave];
+    WaveQueue<T> &Q = s_q[ZPASS ? 0 : wave];
     WaveQueueA &QA = s_qa[wave];
     typedef typename Lut<T>::type L2;
     const L2 *lut = Lut<T>::ptr(a);
@@ -597,9 +599,8 @@ __global__ void __launch_bounds__(kBlock)
         const __amdgpu_buffer_rsrc_t r_lut = plane_rsrc(uni_ptr(a.lut64), (uint32_t)a.lut64_bytes);
         const __amdgpu_buffer_rsrc_t r_gate = plane_rsrc(uni_ptr(a.gate + kt.off), tnpx * 8u);
         // uniform flags as one scalar word.  Bit 0: the depth-interval test runs (spherical targets whose first
-        // projection is within half a pixel, and not in the z-buffer fill pass, which needs every point inside
-        // the image).  Bit 1: the division-free coarse elevation.
-        const int flags = uni((TM == MODEL_SPHERICAL && st.early != 0 && !(ZB && a.zpass) ? 1 : 0) | (st.el45 != 0 ? 2 : 0));
+        // projection is within half a pixel).  Bit 1: the division-free coarse elevation.
+        const int flags = uni((TM == MODEL_SPHERICAL && st.early != 0 ? 1 : 0) | (st.el45 != 0 ? 2 : 0));
         const __amdgpu_buffer_rsrc_t r_tatt =
             NCH == 5 ? (BF ? plane_rsrc(uni_ptr(a.att4h + kt.off), tnpx * 8u) : plane_rsrc(uni_ptr(a.att4 + kt.off), tnpx * 16u))
                      : (BF ? plane_rsrc(uni_ptr(a.att1h + kt.off), tnpx * 2u) : plane_rsrc(uni_ptr(a.att1 + kt.off), tnpx * 4u));
@@ -811,12 +812,16 @@ __global__ void __launch_bounds__(kBlock)
         // point lands on.  Invalid target depths hold a large negative sentinel, so one bound on the largest
         // |D - zeta| also rejects them.  Tested in FP64 in both paths (the taps are exact in FP64): a mask
         // decision does not depend on the evaluation precision.
-        auto gate_at = [&](float (&tD)[12], int x0, int y0, double zeta) {
+        auto load_taps = [&](float (&tD)[12], int x0, int y0, float &dmin, float &dmax) {
             load_stencil<float, 4>(tD, [&](int vo, int so) { return ld_f32(r_tdep, vo, so); },
                                    ((int)__umul24((uint32_t)(y0 - 1), (uint32_t)Wt) + (x0 - 1)) * 4, Wt * 4);
-            float dmin = tD[0], dmax = tD[0];
+            dmin = dmax = tD[0];
 #pragma unroll
             for (int k = 1; k < 12; ++k) { dmin = fminf(dmin, tD[k]); dmax = fmaxf(dmax, tD[k]); }
+        };
+        auto gate_at = [&](float (&tD)[12], int x0, int y0, double zeta) {
+            float dmin, dmax;
+            load_taps(tD, x0, y0, dmin, dmax);
             return fmax((double)dmax - zeta, zeta - (double)dmin) <= taud_gate;
         };
 
@@ -863,13 +868,23 @@ __global__ void __launch_bounds__(kBlock)
                     du = u - (double)x0; dv = v - (double)y0;
                     al = (T)du; be = (T)dv;
                 }
-                if (ZB && ok && a.zpass) {
+                if (ZPASS && ok) {
                     // z-buffer pass: keep the nearest predicted depth per target cell (depths are positive, so
-                    // their FP32 bit patterns order like the values); nothing queued
-                    atomicMin(zb + y0 * Wt + x0, __float_as_uint((float)zeta));
-                    ok = false;
+                    // their FP32 bit patterns order like the values); nothing queued.  An atomic goes to memory
+                    // (agent scope spans the XCDs' L2s) and the pass is bound by their number, 3.5e10 / s, so a
+                    // point that no decision can depend on skips it.  A point Q drops a point P of its cell
+                    // only if f32(zeta_Q) < f32(zeta_P) - tau, and P matters only if it passes the cell's
+                    // occlusion gate: zeta_P <= dmin + tau, and the taps span at most 2 tau.  So Q matters only
+                    // below dmin (+ FP32 rounding of zeta_P, 6e-8 relative; the margin is 1e-6), in cells with
+                    // such a span.  150 keyframes of 128x1024, 1200 pairs: the pass 3646 -> 943 us (with phase 1a's
+                    // interval test and an instantiation of its own, 77 VGPRs).
+                    float tD[12], dmin, dmax;
+                    load_taps(tD, x0, y0, dmin, dmax);
+                    const double lo = (double)dmin;
+                    if ((double)dmax - lo <= 2.0 * taud_gate + 1e-6 && (double)(float)zeta <= lo + 1e-6 * (lo + taud_gate))
+                        atomicMin(zb + y0 * Wt + x0, __float_as_uint((float)zeta));
                 }
-                if (ok) {
+                if (!ZPASS && ok) {
                     if (DBG) { a.dbg_status[pix] = 4; a.dbg_cell[pix] = make_int2(x0, y0); }
                     float tD[12];
                     const bool gate = gate_at(tD, x0, y0, zeta);
@@ -877,7 +892,7 @@ __global__ void __launch_bounds__(kBlock)
                     // differ between exact arithmetic and any rounding of it, and the point passes the gate in
                     // its cell or in a cell across that boundary (otherwise no rounding changes its outcome)
                     const bool bu = fabs(du - 0.5) > 0.5 - kBandPx, bv = fabs(dv - 0.5) > 0.5 - kBandPx;
-                    band = (bu || bv) && (DBG || pass) && (ZB ? !a.zpass : true);
+                    band = (bu || bv) && (DBG || pass);
                     // (rare: a wave-uniform branch, so the common path carries none of it)
                     if (__builtin_expect(__ballot(band && !gate) != 0, 0)) {
                         if (band && !gate) {
@@ -900,7 +915,7 @@ __global__ void __launch_bounds__(kBlock)
                     bool vis = gate && pass;
                     // z-buffer variant: also no more than tau behind the nearest of the pair's own points in this
                     // cell (both depths as FP32, compared in FP64)
-                    if (ZB && vis)
+                    if (ZTEST && vis)
                         vis = (double)(float)zeta - (double)__uint_as_float(zb[y0 * Wt + x0]) <= taud_gate;
                     if (vis) {
                         const T w00 = (T(1) - al) * (T(1) - be), w01 = al * (T(1) - be);
@@ -919,6 +934,7 @@ __global__ void __launch_bounds__(kBlock)
                     }
                 }
             }
+            if (ZPASS) return;
             n_band += __popcll(__ballot(band));
             // append the valid lanes to phase 2's queue in lane (= pixel) order
             const uint64_t mask = __ballot(valid);
@@ -994,7 +1010,7 @@ __global__ void __launch_bounds__(kBlock)
             // kernels into pinhole targets.  The next chunk's loads, one chunk ahead, go ahead of that branch
             // (never inside it: fetch also advances the next chunk's row and column), elsewhere after the
             // unprojection has its operands.
-            constexpr bool kDepthBranch = ZB || (!F32 && TM == MODEL_PINHOLE);
+            constexpr bool kDepthBranch = ZTEST || (!F32 && TM == MODEL_PINHOLE);
             if (kDepthBranch && cbase + 64 < px1) cur = fetch(cbase + 64);
             const float Ds = pix < px1 ? L.d : 0.f;
             if (DBG && pix < px1) a.dbg_status[pix] = Ds > 0.f ? 2 : 1;
@@ -1049,6 +1065,10 @@ __global__ void __launch_bounds__(kBlock)
                 if (flags & 1) {
                     const float2 g = ld_f32x2(r_gate, (int)(__umul24((uint32_t)kr, (uint32_t)Wt) + kc) * 8);
                     pass = zf >= g.x && zf <= g.y;
+                    // z-buffer pass: only points in front of the smallest tap of a cell that can pass the gate
+                    // enter it (phase 1b has the exact test).  g.y is that tap's largest over the four cells,
+                    // plus tau, widened by 1e-6 relative, which covers zf's 2e-7 and the rounding here (1.2e-7).
+                    if (ZPASS) pass = zf <= g.y - (float)taud_gate;
                 }
                 // debug launches take every projected point through phase 1b (complete per-pixel statuses) and
                 // apply the interval test's verdict at the end
@@ -1100,6 +1120,7 @@ __global__ void __launch_bounds__(kBlock)
             __builtin_amdgcn_wave_barrier();
         }
 
+        if (ZPASS) continue;   // nothing but the z-buffers to leave
         // the wave's totals (fixed order: deterministic), value k in lane k, one store per item
         double outv = 0.0;
         if (!ADJ && F32) {
@@ -1180,7 +1201,7 @@ template <int NCH, int SM, int TM>
 static void launch_adj_t(const EvalArgs &a, int item_base, int n_items, int grid, hipStream_t st)
 {
     if (a.zbuf)
-        hipLaunchKernelGGL((eval_kernel<float, NCH, SM, TM, 1, false, true, true>), dim3(grid), dim3(kBlock), 0, st, a,
+        hipLaunchKernelGGL((eval_kernel<float, NCH, SM, TM, 1, false, true, 1>), dim3(grid), dim3(kBlock), 0, st, a,
                            item_base, n_items);
     else
         hipLaunchKernelGGL((eval_kernel<float, NCH, SM, TM, 1, false, true>), dim3(grid), dim3(kBlock), 0, st, a,
@@ -1259,13 +1280,13 @@ static void launch_eval_t(const EvalArgs &a, int item_base, int n_items, int gri
 {
     if constexpr (std::is_same<T, float>::value) {
         if (a.bf16) {
-            hipLaunchKernelGGL((eval_kernel<T, NCH, SM, TM, GM, DBG, false, false, true>), dim3(grid), dim3(kBlock), 0,
+            hipLaunchKernelGGL((eval_kernel<T, NCH, SM, TM, GM, DBG, false, 0, true>), dim3(grid), dim3(kBlock), 0,
                                st, a, item_base, n_items);
             return;
         }
     }
     if (a.zbuf)
-        hipLaunchKernelGGL((eval_kernel<T, NCH, SM, TM, GM, DBG, false, true>), dim3(grid), dim3(kBlock), 0, st, a,
+        hipLaunchKernelGGL((eval_kernel<T, NCH, SM, TM, GM, DBG, false, 1>), dim3(grid), dim3(kBlock), 0, st, a,
                            item_base, n_items);
     else
         hipLaunchKernelGGL((eval_kernel<T, NCH, SM, TM, GM, DBG>), dim3(grid), dim3(kBlock), 0, st, a, item_base,
@@ -1309,6 +1330,21 @@ void launch_eval(const EvalArgs &a, int precision, int channels, int grad_mode, 
         if (debug) launch_eval_cfg<float, true>(a, channels, grad_mode, src_model, tgt_model, item_base, n_items, grid, st);
         else launch_eval_cfg<float, false>(a, channels, grad_mode, src_model, tgt_model, item_base, n_items, grid, st);
     }
+}
+
+void launch_zbuffer_pass(const EvalArgs &a, int src_model, int tgt_model, int item_base, int n_items, int grid,
+                         hipStream_t st)
+{
+#define PBA_ZPASS(SM, TM)                                                                                         \
+    hipLaunchKernelGGL((eval_kernel<float, 2, SM, TM, 0, false, false, 2>), dim3(grid), dim3(kBlock), 0, st, a,  \
+                       item_base, n_items)
+    switch ((src_model << 1) | tgt_model) {
+    case 0: PBA_ZPASS(MODEL_PINHOLE, MODEL_PINHOLE); break;
+    case 1: PBA_ZPASS(MODEL_PINHOLE, MODEL_SPHERICAL); break;
+    case 2: PBA_ZPASS(MODEL_SPHERICAL, MODEL_PINHOLE); break;
+    default: PBA_ZPASS(MODEL_SPHERICAL, MODEL_SPHERICAL); break;
+    }
+#undef PBA_ZPASS
 }
 
 // ------------------------------------------------------------------ per-pair reduction and expansion (FP64)

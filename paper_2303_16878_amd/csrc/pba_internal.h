@@ -108,11 +108,9 @@ struct EvalArgs {
     // loss adjoint outputs (adjoint launches only): arenas laid out like the images
     float *g_int, *g_dep, *g_nrm;
     double adj_scale;
-    // z-buffer occlusion variant (nullptr: off): per pair, Ht * Wt FP32 depth bits at zbuf + zoff[pair];
-    // zpass = 1 fills it (atomic minimum per cell) instead of evaluating
+    // z-buffer occlusion variant (nullptr: off): per pair, Ht * Wt FP32 depth bits at zbuf + zoff[pair]
     uint32_t *zbuf;
     const int64_t *zoff;
-    int32_t zpass;
     int32_t bf16;                // intensity / normal planes in BF16 (att4h, att1h)
     // per-pixel inspection outputs (debug launches only)
     uint8_t *dbg_status;
@@ -126,6 +124,10 @@ void launch_pair_setup(const double *poses, const int2 *pairs, int P, const Sens
                        const KfDev *kfs, PairDev *out, uint32_t *counters, int ncounters, hipStream_t st);
 void launch_eval(const EvalArgs &a, int precision, int channels, int grad_mode, int src_model, int tgt_model,
                  bool debug, int item_base, int n_items, int grid, hipStream_t st);
+// Fill the pairs' z-buffers (atomic minimum of the predicted depths per target cell) from the items of one
+// model pair.
+void launch_zbuffer_pass(const EvalArgs &a, int src_model, int tgt_model, int item_base, int n_items, int grid,
+                         hipStream_t st);
 void launch_eval_adjoint(const EvalArgs &a, int channels, int src_model, int tgt_model, int item_base, int n_items,
                          int grid, hipStream_t st);
 void launch_pose_grad(const double *b, const float *delta, double scale, float *grad, int N, hipStream_t st);

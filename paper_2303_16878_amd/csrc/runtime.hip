@@ -595,14 +595,12 @@ void zbuffer_pass(pba_ctx *c, const double *poses, hipStream_t st, const WorkBuf
     std::memcpy(&fill, &inf2, 8);
     launch_fill(P_<double>(c->zbuf), (c->zcells + 1) / 2, fill, st);
     EvalArgs a = make_args(c);
-    a.partials = w.partials;
-    a.zpass = 1;
     const int ngrp = (int)c->groups.size();
     for (int g = 0; g < ngrp; ++g) {
         const auto &G = c->groups[g];
         a.counter = w.counters + g * kXcd * kCtrStride;
-        launch_eval(a, c->cfg.precision, c->cfg.channels, c->cfg.grad_mode, G.sm, G.tm, false, G.base, G.count,
-                    std::max(1, std::min(G.count, c->grid)), st);
+        // (half as many workgroups again as the evaluation: the pass keeps no sums and six of its waves fit a SIMD)
+        launch_zbuffer_pass(a, G.sm, G.tm, G.base, G.count, std::max(1, std::min(G.count, c->grid + c->grid / 2)), st);
     }
     launch_pair_setup(poses, P_<int2>(c->pairs_d), c->P, P_<SensorDev>(c->L().sensors_d), P_<KfDev>(c->L().kfs_d),
                       P_<PairDev>(c->pair_dev), w.counters, ngrp * kXcd, st);

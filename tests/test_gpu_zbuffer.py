@@ -108,3 +108,28 @@ def test_zbuffer_config_errors(pba):
     cfg.occlusion_zbuffer = 1
     cfg.storage_bf16 = 1          # the z-buffer variant has no BF16 instantiation
     assert pba.load_library().pba_create(ctypes.byref(cfg), ctypes.byref(h)) == pba.PBA_EINVAL
+
+
+@pytest.mark.parametrize("name,prec,tau", [("lidar_mini", "F32", 1.0), ("lidar_mini", "F64", 0.25),
+                                           ("joint_mini", "F32", 1.0), ("rgbd_small", "F32", 0.1)])
+def test_occluders_unseen_by_the_targets(pba, name, prec, tau, request):
+    """Source images with foreign objects in front of a third of the pixels, at depths spread around tau
+    (from just inside the gate to far in front of it): the points that enter the z-buffer are chosen by
+    bounds on the target's taps, and the masks must be those of a z-buffer of every point."""
+    prob = _with_zbuffer(request.getfixturevalue(name))
+    prob.params = dict(prob.params, occ_tau_pinhole=tau, occ_tau_spherical=tau)
+    rng = np.random.default_rng(11)
+    prob.depth = [d.copy() for d in prob.depth]
+    for d in prob.depth[::2]:
+        H, W = d.shape
+        for _ in range(H * W // 300):
+            y, x, h, w = rng.integers(H), rng.integers(W), rng.integers(1, 12), rng.integers(1, 24)
+            d[y:y + h, x:x + w] -= np.float32(tau * rng.uniform(0.9, 6.0))
+    precision = pba.PBA_F64 if prec == "F64" else pba.PBA_F32
+    dropped = 0
+    with pba.context_for_problem(prob, precision=precision) as ctx:
+        for k in range(min(len(prob.pairs), 12)):
+            m = compare_pair_masks(ctx, prob, prob.init_poses, k)
+            assert m["n_bad"] == 0, (k, m["n_mismatch"], m["bad_idx"])
+            dropped += int((m["orc"]["status"] == oracle.ST_ZOCCLUDED).sum())
+    assert dropped > 0
