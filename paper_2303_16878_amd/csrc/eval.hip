@@ -22,6 +22,7 @@
 
 #include "pba_internal.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace pba {
@@ -511,7 +512,7 @@ __global__ void __launch_bounds__(kBlock)
     __attribute__((amdgpu_waves_per_eu(
         std::is_same<T, float>::value && !DBG && !ADJ && ZB != 2 && NCH == 2 && SM == MODEL_PINHOLE && TM == MODEL_PINHOLE ? 6
                                                                                                              : 1)))
-    eval_kernel(EvalArgs a, int item_base, int n_items)
+    eval_kernel(EvalArgs a, int item_base, int n_items, int n_static)
 {
     constexpr bool ZTEST = ZB == 1, ZPASS = ZB == 2;
     __shared__ WaveQueue<T> s_q[ZPASS ? 1 : kBlock / 64];
@@ -524,28 +525,44 @@ __global__ void __launch_bounds__(kBlock)
     const L2 *lut = Lut<T>::ptr(a);
     constexpr bool F32 = std::is_same<T, float>::value;
 
-    // The items of a launch form kXcd contiguous queues; workgroups are dispatched round-robin
-    // over the XCDs, so the waves of workgroup w drain queue w % kXcd first (items that share target
-    // images stay on one XCD's L2), then help with the others.  Each wave takes items on its own
-    // and leaves once all queues are exhausted: no wave waits for another.
-    int q = 0;   // lane 0: queues tried so far
+    // The items of a launch form kXcd contiguous queues; workgroups are dispatched round-robin over the
+    // XCDs, so the waves of workgroup w work on queue w % kXcd first (items that share target images stay
+    // on one XCD's L2), then help with the others.  The waves of the first n_static workgroups (those the
+    // chip holds at once) start on an item of their own, by position; the rest of a queue is taken through
+    // its counter, each wave by itself (no wave waits for another), and a wave leaves once every queue is
+    // exhausted.  A counter hands out an item every ~85 ns and its round trip takes 1 to 2 us; a launch of at
+    // most one item per wave uses none of it (56 pairs of 240x320 in 1024-pixel items: 95 -> 73 us).
+    int next = -1, cur = (int)blockIdx.x % kXcd;   // cur: the queue being drained
+    if ((int)blockIdx.x < n_static) {
+        const int slot = (int)blockIdx.x / kXcd * (kBlock / 64) + wave;
+        const int lo = (int)((int64_t)n_items * cur / kXcd), hi = (int)((int64_t)n_items * (cur + 1) / kXcd);
+        if (slot < hi - lo) next = lo + slot;
+    }
     for (;;) {
-        int got = -1;
-        if (lane == 0) {
-            while (q < kXcd) {
-                const int x = ((int)blockIdx.x + q) % kXcd;
-                const int lo = (int)((int64_t)n_items * x / kXcd), hi = (int)((int64_t)n_items * (x + 1) / kXcd);
-                // a plain read first: an exhausted queue costs no atomic (thousands of waves leave at the end)
-                uint32_t *const ctr = a.counter + x * kCtrStride;
-                const uint32_t seen = __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (seen < (uint32_t)(hi - lo)) {
-                    const int v = (int)atomicAdd(ctr, 1u);
-                    if (v < hi - lo) { got = lo + v; break; }
-                }
-                ++q;
+        int it = next;
+        next = -1;
+        // a plain read goes before each atomic: an exhausted queue costs no atomic (thousands of waves leave at the
+        // end).  Lane 0 reads the queue in hand; once that is exhausted, lanes 0..7 read all eight counters.
+        for (int probe = 1; it < 0 && probe <= kXcd; ) {
+            int l = lane;   // opaque, or the queue bounds of each lane would be kept in registers through the item
+            asm volatile("" : "+v"(l));
+            const int x = (cur + l) % kXcd;
+            const int lo = (int)((int64_t)n_items * x / kXcd), hi = (int)((int64_t)n_items * (x + 1) / kXcd);
+            const int own = (n_static - x + kXcd - 1) / kXcd * (kBlock / 64);   // items started by position
+            uint32_t *const ctr = a.counter + x * kCtrStride;
+            bool has = l < probe && hi - lo > own;
+            if (has) has = __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)(hi - lo - own);
+            const uint64_t some = __ballot(has);
+            if (some == 0) { probe = probe == 1 ? kXcd : kXcd + 1; continue; }
+            const int f = __ffsll((unsigned long long)some) - 1;
+            int got = -1;
+            if (l == f) {
+                const int v = (int)atomicAdd(ctr, 1u);
+                if (v < hi - lo - own) got = lo + own + v;
             }
+            it = __builtin_amdgcn_readlane(got, f);
+            cur = (cur + f) % kXcd;
         }
-        const int it = __builtin_amdgcn_readfirstlane(got);   // lane 0's
         if (it < 0) break;
         const int item = a.item_map ? a.item_map[item_base + it] : item_base + it;
         const int pair = __builtin_amdgcn_readfirstlane(a.item_pair[item]);
@@ -1197,15 +1214,40 @@ void launch_gate_plane(const float *dep, float2 *gate, int H, int W, double tau,
     hipLaunchKernelGGL(gate_plane_kernel, dim3((W + 127) / 128, H), dim3(128), 0, st, dep, gate, H, W, tau);
 }
 
+// One persistent launch of an evaluation kernel: at most `grid` workgroups and no more than give each
+// wave one item (per queue), so that few items spread one wave to a SIMD.  n_static: the workgroups the chip
+// holds at once (the kernel's occupancy); a workgroup beyond them may start only when others have left,
+// so it gets no item by position.
+template <typename K>
+static void launch_items(K kernel, int per_cu, const EvalArgs &a, int item_base, int n_items, int grid, hipStream_t st)
+{
+    if (n_items <= 0) return;
+    constexpr int kWaves = kBlock / 64;
+    const int per_queue = (n_items + kXcd - 1) / kXcd;
+    grid = std::max(1, std::min(grid, (per_queue + kWaves - 1) / kWaves * kXcd));
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), 0, st, a, item_base, n_items, std::min(grid, per_cu * a.num_cu));
+}
+template <typename K>
+static int blocks_per_cu(K kernel)
+{
+    int n = 0;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, kBlock, 0) == hipSuccess ? n : 0;
+}
+// (the occupancy is a property of the kernel, asked once; the macro's value)
+#define PBA_LAUNCH_ITEMS(...)                                                              \
+    [&]() -> int {                                                                         \
+        static const int per_cu = blocks_per_cu(__VA_ARGS__);                              \
+        launch_items(__VA_ARGS__, per_cu, a, item_base, n_items, grid, st);                \
+        return per_cu;                                                                     \
+    }()
+
 template <int NCH, int SM, int TM>
 static void launch_adj_t(const EvalArgs &a, int item_base, int n_items, int grid, hipStream_t st)
 {
     if (a.zbuf)
-        hipLaunchKernelGGL((eval_kernel<float, NCH, SM, TM, 1, false, true, 1>), dim3(grid), dim3(kBlock), 0, st, a,
-                           item_base, n_items);
+        PBA_LAUNCH_ITEMS(eval_kernel<float, NCH, SM, TM, 1, false, true, 1>);
     else
-        hipLaunchKernelGGL((eval_kernel<float, NCH, SM, TM, 1, false, true>), dim3(grid), dim3(kBlock), 0, st, a,
-                           item_base, n_items);
+        PBA_LAUNCH_ITEMS(eval_kernel<float, NCH, SM, TM, 1, false, true>);
 }
 
 void launch_eval_adjoint(const EvalArgs &a, int channels, int sm, int tm, int item_base, int n_items, int grid,
@@ -1276,68 +1318,62 @@ void launch_delta_to_dx(const float *delta, double *dx, int N, hipStream_t st)
 }
 
 template <typename T, int NCH, int SM, int TM, int GM, bool DBG>
-static void launch_eval_t(const EvalArgs &a, int item_base, int n_items, int grid, hipStream_t st)
+static int launch_eval_t(const EvalArgs &a, int item_base, int n_items, int grid, hipStream_t st)
 {
     if constexpr (std::is_same<T, float>::value) {
         if (a.bf16) {
-            hipLaunchKernelGGL((eval_kernel<T, NCH, SM, TM, GM, DBG, false, 0, true>), dim3(grid), dim3(kBlock), 0,
-                               st, a, item_base, n_items);
-            return;
+            return PBA_LAUNCH_ITEMS(eval_kernel<T, NCH, SM, TM, GM, DBG, false, 0, true>);
         }
     }
     if (a.zbuf)
-        hipLaunchKernelGGL((eval_kernel<T, NCH, SM, TM, GM, DBG, false, 1>), dim3(grid), dim3(kBlock), 0, st, a,
-                           item_base, n_items);
+        return PBA_LAUNCH_ITEMS(eval_kernel<T, NCH, SM, TM, GM, DBG, false, 1>);
     else
-        hipLaunchKernelGGL((eval_kernel<T, NCH, SM, TM, GM, DBG>), dim3(grid), dim3(kBlock), 0, st, a, item_base,
-                           n_items);
+        return PBA_LAUNCH_ITEMS(eval_kernel<T, NCH, SM, TM, GM, DBG>);
 }
 
 template <typename T, int NCH, int GM, bool DBG>
-static void launch_eval_models(const EvalArgs &a, int sm, int tm, int item_base, int n_items, int grid,
+static int launch_eval_models(const EvalArgs &a, int sm, int tm, int item_base, int n_items, int grid,
                                hipStream_t st)
 {
     if (sm == MODEL_PINHOLE && tm == MODEL_PINHOLE)
-        launch_eval_t<T, NCH, MODEL_PINHOLE, MODEL_PINHOLE, GM, DBG>(a, item_base, n_items, grid, st);
+        return launch_eval_t<T, NCH, MODEL_PINHOLE, MODEL_PINHOLE, GM, DBG>(a, item_base, n_items, grid, st);
     else if (sm == MODEL_PINHOLE)
-        launch_eval_t<T, NCH, MODEL_PINHOLE, MODEL_SPHERICAL, GM, DBG>(a, item_base, n_items, grid, st);
+        return launch_eval_t<T, NCH, MODEL_PINHOLE, MODEL_SPHERICAL, GM, DBG>(a, item_base, n_items, grid, st);
     else if (tm == MODEL_PINHOLE)
-        launch_eval_t<T, NCH, MODEL_SPHERICAL, MODEL_PINHOLE, GM, DBG>(a, item_base, n_items, grid, st);
+        return launch_eval_t<T, NCH, MODEL_SPHERICAL, MODEL_PINHOLE, GM, DBG>(a, item_base, n_items, grid, st);
     else
-        launch_eval_t<T, NCH, MODEL_SPHERICAL, MODEL_SPHERICAL, GM, DBG>(a, item_base, n_items, grid, st);
+        return launch_eval_t<T, NCH, MODEL_SPHERICAL, MODEL_SPHERICAL, GM, DBG>(a, item_base, n_items, grid, st);
 }
 
 template <typename T, bool DBG>
-static void launch_eval_cfg(const EvalArgs &a, int channels, int gm, int sm, int tm, int item_base, int n_items,
+static int launch_eval_cfg(const EvalArgs &a, int channels, int gm, int sm, int tm, int item_base, int n_items,
                             int grid, hipStream_t st)
 {
     if (channels == 5) {
-        if (gm == 0) launch_eval_models<T, 5, 0, DBG>(a, sm, tm, item_base, n_items, grid, st);
-        else launch_eval_models<T, 5, 1, DBG>(a, sm, tm, item_base, n_items, grid, st);
+        if (gm == 0) return launch_eval_models<T, 5, 0, DBG>(a, sm, tm, item_base, n_items, grid, st);
+        else return launch_eval_models<T, 5, 1, DBG>(a, sm, tm, item_base, n_items, grid, st);
     } else {
-        if (gm == 0) launch_eval_models<T, 2, 0, DBG>(a, sm, tm, item_base, n_items, grid, st);
-        else launch_eval_models<T, 2, 1, DBG>(a, sm, tm, item_base, n_items, grid, st);
+        if (gm == 0) return launch_eval_models<T, 2, 0, DBG>(a, sm, tm, item_base, n_items, grid, st);
+        else return launch_eval_models<T, 2, 1, DBG>(a, sm, tm, item_base, n_items, grid, st);
     }
 }
 
-void launch_eval(const EvalArgs &a, int precision, int channels, int grad_mode, int src_model, int tgt_model,
+int launch_eval(const EvalArgs &a, int precision, int channels, int grad_mode, int src_model, int tgt_model,
                  bool debug, int item_base, int n_items, int grid, hipStream_t st)
 {
     if (precision == 1) {
-        if (debug) launch_eval_cfg<double, true>(a, channels, grad_mode, src_model, tgt_model, item_base, n_items, grid, st);
-        else launch_eval_cfg<double, false>(a, channels, grad_mode, src_model, tgt_model, item_base, n_items, grid, st);
+        if (debug) return launch_eval_cfg<double, true>(a, channels, grad_mode, src_model, tgt_model, item_base, n_items, grid, st);
+        else return launch_eval_cfg<double, false>(a, channels, grad_mode, src_model, tgt_model, item_base, n_items, grid, st);
     } else {
-        if (debug) launch_eval_cfg<float, true>(a, channels, grad_mode, src_model, tgt_model, item_base, n_items, grid, st);
-        else launch_eval_cfg<float, false>(a, channels, grad_mode, src_model, tgt_model, item_base, n_items, grid, st);
+        if (debug) return launch_eval_cfg<float, true>(a, channels, grad_mode, src_model, tgt_model, item_base, n_items, grid, st);
+        else return launch_eval_cfg<float, false>(a, channels, grad_mode, src_model, tgt_model, item_base, n_items, grid, st);
     }
 }
 
 void launch_zbuffer_pass(const EvalArgs &a, int src_model, int tgt_model, int item_base, int n_items, int grid,
                          hipStream_t st)
 {
-#define PBA_ZPASS(SM, TM)                                                                                         \
-    hipLaunchKernelGGL((eval_kernel<float, 2, SM, TM, 0, false, false, 2>), dim3(grid), dim3(kBlock), 0, st, a,  \
-                       item_base, n_items)
+#define PBA_ZPASS(SM, TM) PBA_LAUNCH_ITEMS(eval_kernel<float, 2, SM, TM, 0, false, false, 2>)
     switch ((src_model << 1) | tgt_model) {
     case 0: PBA_ZPASS(MODEL_PINHOLE, MODEL_PINHOLE); break;
     case 1: PBA_ZPASS(MODEL_PINHOLE, MODEL_SPHERICAL); break;
@@ -1349,11 +1385,14 @@ void launch_zbuffer_pass(const EvalArgs &a, int src_model, int tgt_model, int it
 
 // ------------------------------------------------------------------ per-pair reduction and expansion (FP64)
 
-// One wave per pair: sums the pair's FP64 item partials in item order, then expands S, beta
-// into the 12x12 / 12 blocks over [dx_s; dx_t]:
+// One workgroup per pair: sums the pair's FP64 item partials (kRedG groups of 32 lanes, group g the items g,
+// g + kRedG, ..., then the groups in order: a fixed order, and kRedG x 4 rows in flight where one wave adding them
+// one after the other waited for each: 1000 pairs of 75 items 37 -> 9 us), then expands S, beta into the
+// 12x12 / 12 blocks over [dx_s; dx_t]:
 //   H_tt = D^T S D, H_ss = E^T S E, H_st = E^T S D, H_ts = D^T S E, b_t = D^T beta, b_s = E^T beta
 // with D = blockdiag(R_ot^T, R_ot^T) and E = D A.
-__global__ void __launch_bounds__(64) reduce_pairs_kernel(const double *__restrict__ partials,
+constexpr int kRedG = 8;
+__global__ void __launch_bounds__(32 * kRedG) reduce_pairs_kernel(const double *__restrict__ partials,
                                                           const int32_t *__restrict__ pitems,
                                                           const int32_t *__restrict__ ibeg,
                                                           const int32_t *__restrict__ icnt,
@@ -1362,12 +1401,19 @@ __global__ void __launch_bounds__(64) reduce_pairs_kernel(const double *__restri
 {
     const int p = blockIdx.x;
     const int lane = threadIdx.x;
-    __shared__ double sums[kAcc];
+    __shared__ double red[kRedG][kAcc], sums[kAcc];
     __shared__ double S[36], beta[6], Dm[36], Em[36], SD[36], SE[36];
+    {
+        double s = 0.0;
+        const int b = ibeg[p], n = icnt[p], g = lane / kAcc, k = lane % kAcc;
+#pragma unroll 4
+        for (int i = g; i < n; i += kRedG) s += partials[(int64_t)pitems[b + i] * kAcc + k];
+        red[g][k] = s;
+    }
+    __syncthreads();
     if (lane < kAcc) {
         double s = 0.0;
-        const int b = ibeg[p], n = icnt[p];
-        for (int i = 0; i < n; ++i) s += partials[(int64_t)pitems[b + i] * kAcc + lane];
+        for (int g = 0; g < kRedG; ++g) s += red[g][lane];
         sums[lane] = s;
     }
     __syncthreads();
@@ -1433,7 +1479,7 @@ void launch_reduce_pairs(const void *partials, int precision, const int32_t *pit
 {
     (void)precision;
     if (P <= 0) return;
-    hipLaunchKernelGGL(reduce_pairs_kernel, dim3(P), dim3(64), 0, st, static_cast<const double *>(partials), pitems,
+    hipLaunchKernelGGL(reduce_pairs_kernel, dim3(P), dim3(32 * kRedG), 0, st, static_cast<const double *>(partials), pitems,
                        ibeg, icnt, pairs, pair_out, P);
 }
 

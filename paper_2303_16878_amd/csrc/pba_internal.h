@@ -103,6 +103,7 @@ struct EvalArgs {
     int32_t items_px;
     int32_t lut64_bytes;         // size of the FP64 ray tables (bounds of their buffer loads)
     uint32_t *counter;           // kXcd queue counters of this launch, kCtrStride apart
+    int32_t num_cu;              // compute units of the device
     void *partials;              // double[n_items][kAcc]
     double omega_g, omega_d, omega_n, huber;
     // loss adjoint outputs (adjoint launches only): arenas laid out like the images
@@ -122,8 +123,9 @@ struct EvalArgs {
 // ---- launch wrappers (eval.hip)
 void launch_pair_setup(const double *poses, const int2 *pairs, int P, const SensorDev *sensors,
                        const KfDev *kfs, PairDev *out, uint32_t *counters, int ncounters, hipStream_t st);
-void launch_eval(const EvalArgs &a, int precision, int channels, int grad_mode, int src_model, int tgt_model,
-                 bool debug, int item_base, int n_items, int grid, hipStream_t st);
+// Returns the workgroups of the kernel one compute unit holds; launches nothing when n_items is 0.
+int launch_eval(const EvalArgs &a, int precision, int channels, int grad_mode, int src_model, int tgt_model,
+                bool debug, int item_base, int n_items, int grid, hipStream_t st);
 // Fill the pairs' z-buffers (atomic minimum of the predicted depths per target cell) from the items of one
 // model pair.
 void launch_zbuffer_pass(const EvalArgs &a, int src_model, int tgt_model, int item_base, int n_items, int grid,

@@ -72,6 +72,7 @@ struct pba_ctx {
 
     // items
     int items_px = 4096;    // source pixels per work item (one wave's)
+    int tuned_px = 0;       // the size pba_autotune chose, 0 before any
     int n_items = 0;
     struct Group { int sm, tm, base, count; };
     std::vector<Group> groups;
@@ -432,9 +433,40 @@ pba_status ensure_chol_plan(pba_ctx *c)
     return c->P > 0 ? build_chol_plan(c, c->src_h, c->tgt_h) : build_chol_plan(c, none, none);
 }
 
+EvalArgs make_args(pba_ctx *c);
+
+// Source pixels per work item, unless tuned: 4096, or the smallest multiple of 64 that gives every wave the
+// chip holds (of the launch's grid) at most one item of the largest model group.  Above one item per wave the
+// queue and the ends of items (about 1100 instructions and a partial batch each) cost more than finer items
+// balance: 7000 pairs of 64x1024 take 3.66 ms in items of 4096, 4.41 in items of 2048.  Below, waves without
+// an item idle: 20 pairs of 120x160 take 85 / 17 / 13 us in items of 4096 / 512 / 128, 56 pairs of 240x320
+// 135 / 75 us in items of 4096 / 1024.
+int default_items_px(pba_ctx *c, const std::vector<int32_t> &src, const std::vector<int32_t> &tgt)
+{
+    int64_t px[4] = {0, 0, 0, 0};
+    for (size_t p = 0; p < src.size(); ++p) {
+        const KfDev &ks = c->L().kfs_h[src[p]], &kt = c->L().kfs_h[tgt[p]];
+        px[c->sensors[ks.sensor].model * 2 + c->sensors[kt.sensor].model] += (int64_t)ks.H * ks.W;
+    }
+    const int k = (int)(std::max_element(px, px + 4) - px);
+    const int per_cu = launch_eval(make_args(c), c->cfg.precision, c->cfg.channels, c->cfg.grad_mode, k >> 1, k & 1, false,
+                                   0, 0, 0, c->stream);
+    const int64_t waves = std::max<int64_t>(1, std::min<int64_t>((int64_t)per_cu * c->num_cu, c->grid)) * (kBlock / 64);
+    const int64_t size = std::min<int64_t>(4096, std::max<int64_t>(64, ((px[k] + waves - 1) / waves + 63) / 64 * 64));
+    // (a queue that the allocation-free evaluation's array holds in items of 4096 stays one)
+    int64_t items = 0;
+    for (size_t p = 0; p < src.size(); ++p) {
+        const KfDev &ks = c->L().kfs_h[src[p]];
+        items += ((int64_t)ks.H * ks.W + size - 1) / size;
+    }
+    const int64_t need = items * kAcc * 8 + (int64_t)src.size() * kPairOut * 8 + 64 * 1024;
+    return need <= (int64_t)kScratchBytes ? (int)size : 4096;
+}
+
 pba_status build_plan(pba_ctx *c, const std::vector<int32_t> &src, const std::vector<int32_t> &tgt)
 {
     const int P = (int)src.size();
+    c->items_px = c->tuned_px ? c->tuned_px : default_items_px(c, src, tgt);
     // work items: (pair, first source pixel); grouped by (source model, target model),
     // ordered by target keyframe so items sharing a target image run close together
     std::vector<int> order(P);
@@ -561,6 +593,7 @@ EvalArgs make_args(pba_ctx *c)
     a.item_pair = P_<int32_t>(c->item_pair);
     a.item_px0 = P_<int32_t>(c->item_px0);
     a.items_px = c->items_px;
+    a.num_cu = c->num_cu;
     a.partials = c->partials.p;
     a.omega_g = c->cfg.omega_intensity;
     a.omega_d = c->cfg.omega_depth;
@@ -600,7 +633,7 @@ void zbuffer_pass(pba_ctx *c, const double *poses, hipStream_t st, const WorkBuf
         const auto &G = c->groups[g];
         a.counter = w.counters + g * kXcd * kCtrStride;
         // (half as many workgroups again as the evaluation: the pass keeps no sums and six of its waves fit a SIMD)
-        launch_zbuffer_pass(a, G.sm, G.tm, G.base, G.count, std::max(1, std::min(G.count, c->grid + c->grid / 2)), st);
+        launch_zbuffer_pass(a, G.sm, G.tm, G.base, G.count, c->grid + c->grid / 2, st);
     }
     launch_pair_setup(poses, P_<int2>(c->pairs_d), c->P, P_<SensorDev>(c->L().sensors_d), P_<KfDev>(c->L().kfs_d),
                       P_<PairDev>(c->pair_dev), w.counters, ngrp * kXcd, st);
@@ -626,8 +659,7 @@ pba_status run_eval(pba_ctx *c, const double *poses, double *H, double *b, doubl
     for (int g = 0; g < ngrp; ++g) {
         const auto &G = c->groups[g];
         a.counter = w.counters + g * kXcd * kCtrStride;
-        const int grid = std::max(1, std::min(G.count, c->grid));
-        launch_eval(a, c->cfg.precision, c->cfg.channels, c->cfg.grad_mode, G.sm, G.tm, false, G.base, G.count, grid,
+        launch_eval(a, c->cfg.precision, c->cfg.channels, c->cfg.grad_mode, G.sm, G.tm, false, G.base, G.count, c->grid,
                     st);
     }
     if (timed) HIP_OK(hipEventRecord(c->ev1, st));
@@ -1337,8 +1369,7 @@ pba_status pba_loss_backward(pba_ctx *c, double grad_F, float *grad_delta, float
     for (int g = 0; g < ngrp; ++g) {
         const auto &G = c->groups[g];
         a.counter = P_<uint32_t>(c->counters) + g * kXcd * kCtrStride;
-        launch_eval_adjoint(a, c->cfg.channels, G.sm, G.tm, G.base, G.count, std::max(1, std::min(G.count, c->grid)),
-                            c->stream);
+        launch_eval_adjoint(a, c->cfg.channels, G.sm, G.tm, G.base, G.count, c->grid, c->stream);
     }
     HIP_OK(hipGetLastError());
     launch_reduce_pairs(c->partials.p, 1, P_<int32_t>(c->pitems), P_<int32_t>(c->ibeg), P_<int32_t>(c->icnt),
@@ -1478,7 +1509,7 @@ pba_status pba_autotune(pba_ctx *c, pba_tune_point *points, int32_t max_points, 
     int best_px = c->items_px, best_grid = c->grid, n = 0;
     double best = 1e300;
     for (int si = 0; si < 6; ++si) {
-        c->items_px = sizes[si];
+        c->tuned_px = sizes[si];
         if ((s = build_plan(c, c->src_h, c->tgt_h))) return s;
         for (int gi = 0; gi < 3; ++gi) {
             c->grid = c->num_cu * mult[gi];
@@ -1496,7 +1527,7 @@ pba_status pba_autotune(pba_ctx *c, pba_tune_point *points, int32_t max_points, 
             if (ms < best) { best = ms; best_px = sizes[si]; best_grid = c->grid; }
         }
     }
-    c->items_px = best_px;
+    c->tuned_px = best_px;
     c->grid = best_grid;
     if ((s = build_plan(c, c->src_h, c->tgt_h))) return s;
     drop_graph(c);
@@ -1669,8 +1700,7 @@ pba_status pba_debug_pair(pba_ctx *c, int32_t pair, uint8_t *status, float *uv, 
     a.dbg_res = P_<float>(c->dbg_res);
     const int sm = c->sensors[ks.sensor].model, tm = c->sensors[kt.sensor].model;
     const int base = c->pair_item_begin[pair], cnt = c->pair_item_count[pair];
-    launch_eval(a, c->cfg.precision, c->cfg.channels, c->cfg.grad_mode, sm, tm, true, base, cnt,
-                std::max(1, std::min(cnt, c->grid)), c->stream);
+    launch_eval(a, c->cfg.precision, c->cfg.channels, c->cfg.grad_mode, sm, tm, true, base, cnt, c->grid, c->stream);
     HIP_OK(hipGetLastError());
     if (status) HIP_OK(hipMemcpyAsync(status, c->dbg_status.p, npx, hipMemcpyDeviceToHost, c->stream));
     if (uv) HIP_OK(hipMemcpyAsync(uv, c->dbg_uv.p, (size_t)npx * 8, hipMemcpyDeviceToHost, c->stream));
