@@ -54,18 +54,58 @@ __device__ static inline void mtv3(const double *A, const double *v, double *o) 
     o[0] = r0; o[1] = r1; o[2] = r2;
 }
 
-__global__ void pair_setup_kernel(const double *__restrict__ poses, const int2 *__restrict__ pairs, int P,
-                                  const SensorDev *__restrict__ sensors, const KfDev *__restrict__ kfs,
-                                  PairDev *__restrict__ out, uint32_t *counters, int ncounters)
+// Inside an iteration the step is applied here (step.dx): every pair's thread moves its own two poses, the
+// first N threads store the moved poses, and a workgroup after the pairs' sums |dx|, so the update costs no
+// launch of its own.
+constexpr int kSetupBlock = 128;
+__global__ void __launch_bounds__(kSetupBlock) pair_setup_kernel(const double *__restrict__ poses, PoseStep step,
+                                                                 const int2 *__restrict__ pairs, int P,
+                                                                 const SensorDev *__restrict__ sensors,
+                                                                 const KfDev *__restrict__ kfs, PairDev *__restrict__ out,
+                                                                 uint32_t *counters, int ncounters, Stamp stamp)
 {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    const bool move = step.dx && !(step.fail && *step.fail);
+    auto pose = [&](int k, double *o) {
+        const double *x = poses + 12 * (int64_t)k;
+        if (move) boxplus_pose(x, step.dx + (step.off ? (int64_t)step.off[k] : 6 * (int64_t)k), o);
+        else for (int i = 0; i < 12; ++i) o[i] = x[i];
+    };
+    if (step.dx && blockIdx.x + 1 == gridDim.x) {
+        __shared__ double red[kSetupBlock];
+        const int tid = threadIdx.x;
+        double ss = 0.0;
+        for (int k = tid; k < step.N && move; k += blockDim.x) {
+            const double *d = step.dx + (step.off ? (int64_t)step.off[k] : 6 * (int64_t)k);
+            for (int i = 0; i < 6; ++i) ss += d[i] * d[i];
+        }
+        red[tid] = ss;
+        __syncthreads();
+        for (int w = kSetupBlock / 2; w > 0; w >>= 1) {
+            if (tid < w) red[tid] += red[tid + w];
+            __syncthreads();
+        }
+        if (tid == 0) {
+            step.lm->step_norm = sqrt(red[0]);
+            step.lm->fail = move ? 0 : 1;
+        }
+        return;
+    }
     if (p < ncounters) counters[(int64_t)p * kCtrStride] = 0u;
+    if (p == 0) put_stamp(stamp, 0);
+    if (step.dx && p < step.N) {
+        double o[12];
+        pose(p, o);
+        for (int i = 0; i < 12; ++i) step.Xo[12 * (int64_t)p + i] = o[i];
+    }
     if (p >= P) return;
     const int s = pairs[p].x, t = pairs[p].y;
     const SensorDev &ss = sensors[kfs[s].sensor];
     const SensorDev &st = sensors[kfs[t].sensor];
-    const double *Rs = poses + 12 * (int64_t)kfs[s].pose, *ts = Rs + 9;
-    const double *Rt = poses + 12 * (int64_t)kfs[t].pose, *tt = Rt + 9;
+    double Rs[12], Rt[12];
+    pose(kfs[s].pose, Rs);
+    pose(kfs[t].pose, Rt);
+    const double *ts = Rs + 9, *tt = Rt + 9;
     // platform-level relative pose X_t^-1 X_s
     double Rp[9], tp[3], d3[3];
     mtm3(Rt, Rs, Rp);
@@ -107,12 +147,13 @@ __global__ void pair_setup_kernel(const double *__restrict__ poses, const int2 *
     o.tgt = t;
 }
 
-void launch_pair_setup(const double *poses, const int2 *pairs, int P, const SensorDev *sensors, const KfDev *kfs,
-                       PairDev *out, uint32_t *counters, int ncounters, hipStream_t st)
+void launch_pair_setup(const double *poses, const PoseStep &step, const int2 *pairs, int P, const SensorDev *sensors,
+                       const KfDev *kfs, PairDev *out, uint32_t *counters, int ncounters, const Stamp &stamp,
+                       hipStream_t st)
 {
-    const int n = P > ncounters ? P : ncounters;
-    hipLaunchKernelGGL(pair_setup_kernel, dim3((n + 127) / 128), dim3(128), 0, st, poses, pairs, P, sensors, kfs,
-                       out, counters, ncounters);
+    const int n = std::max(std::max(P, ncounters), step.dx ? step.N : 0);
+    hipLaunchKernelGGL(pair_setup_kernel, dim3((n + kSetupBlock - 1) / kSetupBlock + (step.dx ? 1 : 0)),
+                       dim3(kSetupBlock), 0, st, poses, step, pairs, P, sensors, kfs, out, counters, ncounters, stamp);
 }
 
 // ------------------------------------------------------------------ per-pixel evaluation
@@ -1397,10 +1438,11 @@ __global__ void __launch_bounds__(32 * kRedG) reduce_pairs_kernel(const double *
                                                           const int32_t *__restrict__ ibeg,
                                                           const int32_t *__restrict__ icnt,
                                                           const PairDev *__restrict__ pairs,
-                                                          double *__restrict__ out, int P)
+                                                          double *__restrict__ out, int P, Stamp stamp)
 {
     const int p = blockIdx.x;
     const int lane = threadIdx.x;
+    if (p == 0 && lane == 0) put_stamp(stamp, 1);
     __shared__ double red[kRedG][kAcc], sums[kAcc];
     __shared__ double S[36], beta[6], Dm[36], Em[36], SD[36], SE[36];
     {
@@ -1475,12 +1517,12 @@ __global__ void __launch_bounds__(32 * kRedG) reduce_pairs_kernel(const double *
 }
 
 void launch_reduce_pairs(const void *partials, int precision, const int32_t *pitems, const int32_t *ibeg,
-                         const int32_t *icnt, const PairDev *pairs, double *pair_out, int P, hipStream_t st)
+                         const int32_t *icnt, const PairDev *pairs, double *pair_out, int P, const Stamp &stamp, hipStream_t st)
 {
     (void)precision;
     if (P <= 0) return;
     hipLaunchKernelGGL(reduce_pairs_kernel, dim3(P), dim3(32 * kRedG), 0, st, static_cast<const double *>(partials), pitems,
-                       ibeg, icnt, pairs, pair_out, P);
+                       ibeg, icnt, pairs, pair_out, P, stamp);
 }
 
 // ------------------------------------------------------------------ assembly of the 6N x 6N system
@@ -1499,40 +1541,40 @@ void launch_fill(double *p, int64_t n, double v, hipStream_t st)
     hipLaunchKernelGGL(fill_kernel, dim3((unsigned)blocks), dim3(256), 0, st, p, n, v);
 }
 
-// One workgroup per nonzero 6x6 block: sums its contributions in pair order.
-// blk_ent[k] = 4 * pair + quadrant (0 ss, 1 st, 2 ts, 3 tt).
-__global__ void __launch_bounds__(64) assemble_H_kernel(const double *__restrict__ pair_out,
-                                                        const int2 *__restrict__ blk_rc,
-                                                        const int32_t *__restrict__ blk_ptr,
-                                                        const int32_t *__restrict__ blk_ent, int n,
-                                                        double *__restrict__ H)
+// One launch: nonzero 6x6 blocks of H, kBlkPerWg to a workgroup, each entry summing its contributions in pair
+// order (blk_ent[k] = 4 * pair + quadrant: 0 ss, 1 st, 2 ts, 3 tt); then b per pose variable (bk_ent = 2 * pair +
+// side, side 0 = source, 1 = target), one thread per entry; and in the last workgroup the totals F, evaluated,
+// valid and boundary-band count over the pairs, and whether a step evaluated by it is accepted (lm).  Every
+// sum runs in a fixed order.  The rest of H was cleared when the pairs were set.
+constexpr int kBlkPerWg = 7;
+__global__ void __launch_bounds__(256) assemble_kernel(const double *__restrict__ pair_out, int P,
+                                                       const int2 *__restrict__ blk_rc,
+                                                       const int32_t *__restrict__ blk_ptr,
+                                                       const int32_t *__restrict__ blk_ent, int nblk,
+                                                       const int32_t *__restrict__ bk_ptr,
+                                                       const int32_t *__restrict__ bk_ent, int N,
+                                                       double *__restrict__ H, double *__restrict__ b,
+                                                       double *__restrict__ totals, LmState *lm)
 {
-    const int blk = blockIdx.x;
-    const int lane = threadIdx.x;
-    if (lane >= 36) return;
-    const int i = lane / 6, j = lane % 6;
-    double s = 0.0;
-    for (int k = blk_ptr[blk]; k < blk_ptr[blk + 1]; ++k) {
-        const int e = blk_ent[k];
-        const int p = e >> 2, q = e & 3;
-        const int ro = (q >> 1) * 6, co = (q & 1) * 6;
-        s += pair_out[(int64_t)p * kPairOut + 12 * (ro + i) + co + j];
+    const int tid = threadIdx.x, nH = (nblk + kBlkPerWg - 1) / kBlkPerWg;
+    if ((int)blockIdx.x < nH) {
+        const int blk = blockIdx.x * kBlkPerWg + tid / 36, e36 = tid % 36;
+        if (tid >= 36 * kBlkPerWg || blk >= nblk) return;
+        const int i = e36 / 6, j = e36 % 6;
+        double s = 0.0;
+#pragma unroll 4
+        for (int k = blk_ptr[blk]; k < blk_ptr[blk + 1]; ++k) {
+            const int e = blk_ent[k];
+            const int p = e >> 2, q = e & 3;
+            const int ro = (q >> 1) * 6, co = (q & 1) * 6;
+            s += pair_out[(int64_t)p * kPairOut + 12 * (ro + i) + co + j];
+        }
+        const int2 rc = blk_rc[blk];
+        H[(int64_t)(6 * rc.x + i) * (6 * N) + 6 * rc.y + j] = s;
+        return;
     }
-    const int2 rc = blk_rc[blk];
-    H[(int64_t)(6 * rc.x + i) * n + 6 * rc.y + j] = s;
-}
-
-// b per pose variable (bk_ent = 2 * pair + side, side 0 = source, 1 = target), one thread per
-// entry of b in the workgroups before the last, and the totals F, evaluated, valid (and the
-// boundary-band count) summed over pairs in the last workgroup; every sum runs in a fixed order.
-__global__ void __launch_bounds__(256) assemble_b_kernel(const double *__restrict__ pair_out, int P,
-                                                         const int32_t *__restrict__ bk_ptr,
-                                                         const int32_t *__restrict__ bk_ent, int N,
-                                                         double *__restrict__ b, double *__restrict__ totals)
-{
-    const int tid = threadIdx.x;
     if (blockIdx.x + 1 < gridDim.x) {
-        const int r = blockIdx.x * blockDim.x + tid;
+        const int r = (blockIdx.x - nH) * blockDim.x + tid;
         if (r >= 6 * N) return;
         const int k = r / 6, j = r % 6;
         double s = 0.0;
@@ -1557,20 +1599,15 @@ __global__ void __launch_bounds__(256) assemble_b_kernel(const double *__restric
         __syncthreads();
     }
     if (tid < 4) totals[tid] = red[tid][0];
+    if (tid == 0 && lm) lm->accepted = !lm->fail && (!lm->use_lm || red[0][0] < lm->F_cur);
 }
 
 void launch_assemble(const double *pair_out, int P, const int2 *blk_rc, const int32_t *blk_ptr,
                      const int32_t *blk_ent, int nblk, const int32_t *bk_ptr, const int32_t *bk_ent, int N,
-                     double *H, double *b, double *totals, hipStream_t st)
+                     double *H, double *b, double *totals, LmState *lm, hipStream_t st)
 {
-    const int n = 6 * N;
-    launch_fill(H, (int64_t)n * n, 0.0, st);
-    if (nblk > 0)
-        hipLaunchKernelGGL(assemble_H_kernel, dim3(nblk), dim3(64), 0, st, pair_out, blk_rc, blk_ptr, blk_ent, n, H);
-    hipLaunchKernelGGL(assemble_b_kernel, dim3((6 * N + 255) / 256 + 1), dim3(256), 0, st, pair_out, P, bk_ptr, bk_ent,
-                       N, b, totals);
+    hipLaunchKernelGGL(assemble_kernel, dim3((nblk + kBlkPerWg - 1) / kBlkPerWg + (6 * N + 255) / 256 + 1), dim3(256), 0,
+                       st, pair_out, P, blk_rc, blk_ptr, blk_ent, nblk, bk_ptr, bk_ent, N, H, b, totals, lm);
 }
-
-void launch_copy(double *dst, const double *src, int64_t n, hipStream_t st);
 
 }  // namespace pba

@@ -120,9 +120,68 @@ struct EvalArgs {
     float *dbg_res;
 };
 
+struct LmState {
+    double lam, F_cur, F_cand, step_norm;
+    int64_t valid_cur, valid_cand;
+    int32_t fail, accepted, use_lm, iter;
+};
+
+// Device wall-clock stamp (constant-rate counter) into slot 6 + which of the current iteration's log row
+// (logbuf nullptr: none).  The kernels of an iteration write them, one thread each: the damped copy the
+// iteration's begin (which = 2), the pair setup and the per-pair reduction the evaluation's begin and end (0, 1),
+// so every replay of a captured iteration leaves its own durations without launches for them (4.6 us each).
+struct Stamp {
+    const LmState *lm;
+    double *logbuf;
+    int32_t log_cap;
+};
+__device__ __forceinline__ void put_stamp(const Stamp &s, int which)
+{
+    if (!s.logbuf) return;
+    uint64_t *row = reinterpret_cast<uint64_t *>(s.logbuf + kLogRow * (int64_t)min(s.lm->iter, s.log_cap - 1));
+    row[6 + which] = (uint64_t)wall_clock64();
+}
+
+// Rotation of the unit quaternion with imaginary part q (Supplementary; (1, q) normalised beyond |q| = 1).
+__device__ __forceinline__ void quat_rot(double qx, double qy, double qz, double *R)
+{
+    double n2 = qx * qx + qy * qy + qz * qz, w;
+    if (n2 < 1.0) {
+        w = sqrt(1.0 - n2);
+    } else {
+        const double s = 1.0 / sqrt(1.0 + n2);
+        w = s; qx *= s; qy *= s; qz *= s;
+    }
+    R[0] = 1 - 2 * (qy * qy + qz * qz); R[1] = 2 * (qx * qy - qz * w);     R[2] = 2 * (qx * qz + qy * w);
+    R[3] = 2 * (qx * qy + qz * w);     R[4] = 1 - 2 * (qx * qx + qz * qz); R[5] = 2 * (qy * qz - qx * w);
+    R[6] = 2 * (qx * qz - qy * w);     R[7] = 2 * (qy * qz + qx * w);     R[8] = 1 - 2 * (qx * qx + qy * qy);
+}
+
+// o = x exp(d) for one pose (12 doubles) and step (6).
+__device__ __forceinline__ void boxplus_pose(const double *x, const double *d, double *o)
+{
+    double E[9];
+    quat_rot(d[3], d[4], d[5], E);
+    for (int i = 0; i < 3; ++i)
+        for (int j = 0; j < 3; ++j) o[3 * i + j] = x[3 * i] * E[j] + x[3 * i + 1] * E[3 + j] + x[3 * i + 2] * E[6 + j];
+    for (int i = 0; i < 3; ++i) o[9 + i] = x[9 + i] + x[3 * i] * d[0] + x[3 * i + 1] * d[1] + x[3 * i + 2] * d[2];
+}
+
+// The step that a pair setup applies to the poses first (dx nullptr: none): Xo_k = X_k exp(dx_k) for the N
+// poses, kept where the factorisation failed; off as in launch_boxplus.  |dx| and the failure go to lm.
+struct PoseStep {
+    const double *dx;
+    const int32_t *off;
+    double *Xo;
+    int32_t N;
+    const int32_t *fail;
+    LmState *lm;
+};
+
 // ---- launch wrappers (eval.hip)
-void launch_pair_setup(const double *poses, const int2 *pairs, int P, const SensorDev *sensors,
-                       const KfDev *kfs, PairDev *out, uint32_t *counters, int ncounters, hipStream_t st);
+void launch_pair_setup(const double *poses, const PoseStep &step, const int2 *pairs, int P, const SensorDev *sensors,
+                       const KfDev *kfs, PairDev *out, uint32_t *counters, int ncounters, const Stamp &stamp,
+                       hipStream_t st);
 // Returns the workgroups of the kernel one compute unit holds; launches nothing when n_items is 0.
 int launch_eval(const EvalArgs &a, int precision, int channels, int grad_mode, int src_model, int tgt_model,
                 bool debug, int item_base, int n_items, int grid, hipStream_t st);
@@ -136,26 +195,23 @@ void launch_pose_grad(const double *b, const float *delta, double scale, float *
 void launch_delta_to_dx(const float *delta, double *dx, int N, hipStream_t st);
 void launch_reduce_pairs(const void *partials, int precision, const int32_t *pair_items,
                          const int32_t *pair_item_begin, const int32_t *pair_item_count, const PairDev *pairs,
-                         double *pair_out, int P, hipStream_t st);
+                         double *pair_out, int P, const Stamp &stamp, hipStream_t st);
+// H's nonzero 6 x 6 blocks (the rest of H is zero since the pairs were set), b and the totals; with lm, also
+// whether the evaluated step is accepted.
 void launch_assemble(const double *pair_out, int P, const int2 *blk_rc, const int32_t *blk_ptr,
                      const int32_t *blk_ent, int nblk, const int32_t *bk_ptr, const int32_t *bk_ent, int N,
-                     double *H, double *b, double *totals, hipStream_t st);
+                     double *H, double *b, double *totals, LmState *lm, hipStream_t st);
 void launch_fill(double *p, int64_t n, double v, hipStream_t st);
 
 // ---- launch wrappers (solve.hip)
-struct LmState {
-    double lam, F_cur, F_cand, step_norm;
-    int64_t valid_cur, valid_cand;
-    int32_t fail, accepted, use_lm, iter;
-};
 void launch_damp_copy(const double *H, const double *b, double *A, double *rhs, int n, int anchor,
-                      const LmState *lm, double lam_override, hipStream_t st);
+                      const LmState *lm, double lam_override, const Stamp &stamp, hipStream_t st);
 struct CholPlan;
 // The same into the plan's nested-dissection order (plan.n rows, pattern tiles only); also
 // clears *fail.
 void launch_damp_copy_perm(const double *H, const double *b, double *A, double *rhs, int n0, int anchor,
                            const LmState *lm, double lam_override, const CholPlan &plan, int32_t *fail,
-                           hipStream_t st);
+                           const Stamp &stamp, hipStream_t st);
 // Tiles of the Cholesky factor that can be nonzero (host-built from the pair graph with the
 // factorisation's symbolic fill): for block column k, rcnt[k] tile rows i > k at rows + rbeg[k]
 // (device, ascending); for block row k, ccnt[k] tile columns j < k at cols + cbeg[k] (device).
@@ -236,13 +292,11 @@ void launch_normals(const float *dep, void *att4, int bf, int H, int W, const do
 void launch_chol_solve(const double *L, const double *LT, double *Winv, double *x, int n, const CholPlan &plan,
                        const int32_t *fail, hipStream_t st);
 // off: first element of each pose variable's 6 in dx (nested-dissection layout), nullptr = 6 k.
-void launch_boxplus(const double *X, const double *dx, const int32_t *off, double *Xout, int N, const int32_t *fail,
-                    LmState *lm, hipStream_t st);
+void launch_boxplus(const double *X, const double *dx, const int32_t *off, double *Xout, int N, hipStream_t st);
 void launch_gather_step(double *dst, const double *src, const int32_t *off, int N, hipStream_t st);
-void launch_stamp(const LmState *lm, double *logbuf, int log_cap, int which, hipStream_t st);
-void launch_lm_decide(LmState *lm, const double *totals_cand, int64_t nH, double *H_cur, const double *H_cand,
-                      double *b_cur, const double *b_cand, double *X_cur, const double *X_cand, int N,
-                      double *totals_cur, double *logbuf, int log_cap, hipStream_t st);
+void launch_lm_decide(LmState *lm, const double *totals_cand, const int2 *blk_rc, int nblk, double *H_cur,
+                      const double *H_cand, double *b_cur, const double *b_cand, double *X_cur, const double *X_cand,
+                      int N, double *totals_cur, double *logbuf, int log_cap, hipStream_t st);
 void launch_copy(double *dst, const double *src, int64_t n, hipStream_t st);
 
 }  // namespace pba

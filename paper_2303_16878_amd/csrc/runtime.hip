@@ -620,7 +620,16 @@ struct WorkBufs {
 
 WorkBufs ctx_work(pba_ctx *c) { return WorkBufs{P_<uint32_t>(c->counters), c->partials.p, P_<double>(c->pair_out)}; }
 
-void zbuffer_pass(pba_ctx *c, const double *poses, hipStream_t st, const WorkBufs &w)
+// Pair transforms at `poses` (with a step: at the poses it moves them to, which it stores), and cleared queue
+// counters.
+void setup_pairs(pba_ctx *c, const double *poses, const PoseStep &step, uint32_t *counters, int ncounters,
+                 const Stamp &stamp, hipStream_t st)
+{
+    launch_pair_setup(poses, step, P_<int2>(c->pairs_d), c->P, P_<SensorDev>(c->L().sensors_d),
+                      P_<KfDev>(c->L().kfs_d), P_<PairDev>(c->pair_dev), counters, ncounters, stamp, st);
+}
+
+void zbuffer_pass(pba_ctx *c, const double *poses, hipStream_t st, const WorkBufs &w, const Stamp &stamp = Stamp{})
 {
     if (!c->cfg.occlusion_zbuffer || c->P == 0) return;
     const uint64_t inf2 = 0x7F8000007F800000ull;   // two FP32 +inf (a finite double)
@@ -635,27 +644,26 @@ void zbuffer_pass(pba_ctx *c, const double *poses, hipStream_t st, const WorkBuf
         // (half as many workgroups again as the evaluation: the pass keeps no sums and six of its waves fit a SIMD)
         launch_zbuffer_pass(a, G.sm, G.tm, G.base, G.count, c->grid + c->grid / 2, st);
     }
-    launch_pair_setup(poses, P_<int2>(c->pairs_d), c->P, P_<SensorDev>(c->L().sensors_d), P_<KfDev>(c->L().kfs_d),
-                      P_<PairDev>(c->pair_dev), w.counters, ngrp * kXcd, st);
+    setup_pairs(c, poses, PoseStep{}, w.counters, ngrp * kXcd, stamp, st);
 }
 
 // Evaluate at `poses` into (H, b, totals).  Launch order on the context stream:
 // pair setup (also clears the queue counters) -> persistent evaluation per model group
 // -> ordered per-pair reduction/expansion -> assembly.  `timed` brackets the evaluation launches
-// with the context's HIP events; `stamped` with wall-clock stamps into the LM log row (for
-// launches inside a captured iteration, where the events would only keep the last replay).
+// with the context's HIP events; `step` (launches of an iteration) evaluates at the poses moved by the
+// step, which the setup stores in step->Xo, stamps the evaluation into the LM log row (the events would only
+// keep a captured graph's last replay) and decides whether the step is accepted.
 pba_status run_eval(pba_ctx *c, const double *poses, double *H, double *b, double *totals, bool timed,
-                    hipStream_t st, bool stamped = false, const WorkBufs *work = nullptr)
+                    hipStream_t st, const PoseStep *step = nullptr, const WorkBufs *work = nullptr)
 {
     const WorkBufs w = work ? *work : ctx_work(c);
     const int ngrp = (int)c->groups.size();
-    launch_pair_setup(poses, P_<int2>(c->pairs_d), c->P, P_<SensorDev>(c->L().sensors_d), P_<KfDev>(c->L().kfs_d),
-                      P_<PairDev>(c->pair_dev), w.counters, ngrp * kXcd, st);
-    zbuffer_pass(c, poses, st, w);
+    const Stamp stamp = step ? Stamp{step->lm, P_<double>(c->logbuf), c->log_cap} : Stamp{};
+    setup_pairs(c, poses, step ? *step : PoseStep{}, w.counters, ngrp * kXcd, stamp, st);
+    zbuffer_pass(c, step ? step->Xo : poses, st, w, stamp);
     EvalArgs a = make_args(c);
     a.partials = w.partials;
     if (timed) HIP_OK(hipEventRecord(c->ev0, st));
-    if (stamped) launch_stamp(P_<LmState>(c->lm), P_<double>(c->logbuf), c->log_cap, 0, st);
     for (int g = 0; g < ngrp; ++g) {
         const auto &G = c->groups[g];
         a.counter = w.counters + g * kXcd * kCtrStride;
@@ -663,13 +671,12 @@ pba_status run_eval(pba_ctx *c, const double *poses, double *H, double *b, doubl
                     st);
     }
     if (timed) HIP_OK(hipEventRecord(c->ev1, st));
-    if (stamped) launch_stamp(P_<LmState>(c->lm), P_<double>(c->logbuf), c->log_cap, 1, st);
     HIP_OK(hipGetLastError());
     launch_reduce_pairs(w.partials, c->cfg.precision, P_<int32_t>(c->pitems), P_<int32_t>(c->ibeg),
-                        P_<int32_t>(c->icnt), P_<PairDev>(c->pair_dev), w.pair_out, c->P, st);
+                        P_<int32_t>(c->icnt), P_<PairDev>(c->pair_dev), w.pair_out, c->P, stamp, st);
     launch_assemble(w.pair_out, c->P, P_<int2>(c->blk_rc), P_<int32_t>(c->blk_ptr),
                     P_<int32_t>(c->blk_ent), c->nblk, P_<int32_t>(c->bk_ptr), P_<int32_t>(c->bk_ent), c->NP, H, b,
-                    totals, st);
+                    totals, step ? step->lm : nullptr, st);
     HIP_OK(hipGetLastError());
     return PBA_OK;
 }
@@ -685,17 +692,17 @@ void drop_graph(pba_ctx *c)
 
 // Damped, gauge-fixed solve of the current system into dx (the plan's order and layout): lambda
 // from lm, or lam_override when >= 0.
-void enqueue_solve(pba_ctx *c, const LmState *lm, double lam_override, hipStream_t st)
+void enqueue_solve(pba_ctx *c, const LmState *lm, double lam_override, const Stamp &stamp, hipStream_t st)
 {
     const CholPlan &pl = c->chol;
     const int n = pl.n;
     double *A = P_<double>(c->A), *Lf = A + (size_t)n * n, *LTf = Lf + (size_t)n * n;
     if (pl.nd)
         launch_damp_copy_perm(P_<double>(c->H), P_<double>(c->b), A, P_<double>(c->dx), n_sys(c), c->cfg.anchor, lm,
-                              lam_override, pl, P_<int32_t>(c->fail), st);
+                              lam_override, pl, P_<int32_t>(c->fail), stamp, st);
     else
         launch_damp_copy(P_<double>(c->H), P_<double>(c->b), A, P_<double>(c->dx), n, c->cfg.anchor, lm,
-                         lam_override, st);
+                         lam_override, stamp, st);
     launch_cholesky(A, Lf, LTf, n, P_<double>(c->Winv), pl, P_<int32_t>(c->fail), st, P_<double>(c->dx));
     launch_chol_solve(Lf, LTf, P_<double>(c->Winv), P_<double>(c->dx), n, pl, P_<int32_t>(c->fail), st);
 }
@@ -704,16 +711,14 @@ void enqueue_solve(pba_ctx *c, const LmState *lm, double lam_override, hipStream
 // evaluation at the candidate, device-side accept/reject.  Identical launches every iteration.
 pba_status enqueue_iteration(pba_ctx *c, hipStream_t st)
 {
-    const int n = n_sys(c);
     double *totals = P_<double>(c->totals);   // [0..3] current, [4..7] candidate
-    launch_stamp(P_<LmState>(c->lm), P_<double>(c->logbuf), c->log_cap, 2, st);
-    enqueue_solve(c, P_<LmState>(c->lm), -1.0, st);
-    launch_boxplus(P_<double>(c->poses), P_<double>(c->dx), c->chol.nd ? c->chol.pose_off : nullptr,
-                   P_<double>(c->poses_cand), c->NP, P_<int32_t>(c->fail), P_<LmState>(c->lm), st);
-    pba_status s = run_eval(c, P_<double>(c->poses_cand), P_<double>(c->H_cand), P_<double>(c->b_cand), totals + 4,
-                            false, st, true);
+    enqueue_solve(c, P_<LmState>(c->lm), -1.0, Stamp{P_<LmState>(c->lm), P_<double>(c->logbuf), c->log_cap}, st);
+    const PoseStep step{P_<double>(c->dx), c->chol.nd ? c->chol.pose_off : nullptr, P_<double>(c->poses_cand), c->NP,
+                        P_<int32_t>(c->fail), P_<LmState>(c->lm)};
+    pba_status s = run_eval(c, P_<double>(c->poses), P_<double>(c->H_cand), P_<double>(c->b_cand), totals + 4, false, st,
+                            &step);
     if (s) return s;
-    launch_lm_decide(P_<LmState>(c->lm), totals + 4, (int64_t)n * n, P_<double>(c->H), P_<double>(c->H_cand),
+    launch_lm_decide(P_<LmState>(c->lm), totals + 4, P_<int2>(c->blk_rc), c->nblk, P_<double>(c->H), P_<double>(c->H_cand),
                      P_<double>(c->b), P_<double>(c->b_cand), P_<double>(c->poses), P_<double>(c->poses_cand), c->NP,
                      totals, P_<double>(c->logbuf), c->log_cap, st);
     HIP_OK(hipGetLastError());
@@ -746,6 +751,7 @@ pba_status check_ready(pba_ctx *c)
     return PBA_OK;
 }
 
+// Buffers of the system for the pairs just set, cleared.
 pba_status ensure_system(pba_ctx *c)
 {
     const size_t n = (size_t)n_sys(c);
@@ -761,6 +767,10 @@ pba_status ensure_system(pba_ctx *c)
     if ((s = ensure(c, c->dx, n * 8))) return s;
     if ((s = ensure(c, c->lm, sizeof(LmState)))) return s;
     if ((s = ensure(c, c->fail, 16))) return s;
+    // the assembly writes the pairs' blocks only
+    launch_fill(P_<double>(c->H), (int64_t)(n * n), 0.0, c->stream);
+    launch_fill(P_<double>(c->H_cand), (int64_t)(n * n), 0.0, c->stream);
+    HIP_OK(hipGetLastError());
     return PBA_OK;
 }
 
@@ -1124,7 +1134,7 @@ pba_status pba_evaluate_noalloc(pba_ctx *c, pba_eval_out *out)
     if (!base) return fail(c, PBA_EDEVICE, "scratch array of device %d not resolved", c->cfg.device);
     const WorkBufs w{reinterpret_cast<uint32_t *>(base), base + n_cnt, reinterpret_cast<double *>(base + n_cnt + n_part)};
     if ((s = run_eval(c, P_<double>(c->poses), P_<double>(c->H), P_<double>(c->b), P_<double>(c->totals), false,
-                      c->stream, false, &w)))
+                      c->stream, nullptr, &w)))
         return s;
     const size_t n = (size_t)n_sys(c);
     const hipMemcpyKind k = out->on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
@@ -1157,7 +1167,7 @@ pba_status pba_solve_step(pba_ctx *c, double lambda, double *dx, int32_t on_devi
             return s;
         c->system_valid = true;
     }
-    enqueue_solve(c, P_<LmState>(c->lm), lambda, c->stream);
+    enqueue_solve(c, P_<LmState>(c->lm), lambda, Stamp{}, c->stream);
     // the step in pose order
     const double *step = P_<double>(c->dx);
     if (c->chol.nd && dx) {
@@ -1195,8 +1205,7 @@ pba_status pba_apply_step(pba_ctx *c, const double *dx, int32_t on_device)
             if (!std::isfinite(v)) return fail(c, PBA_EINVAL, "non-finite step");
         if ((s = upload(c, c->dx, h.data(), (size_t)n * 8))) return s;
     }
-    launch_boxplus(P_<double>(c->poses), P_<double>(c->dx), nullptr, P_<double>(c->poses_cand), c->NP, nullptr,
-                   nullptr, c->stream);
+    launch_boxplus(P_<double>(c->poses), P_<double>(c->dx), nullptr, P_<double>(c->poses_cand), c->NP, c->stream);
     launch_copy(P_<double>(c->poses), P_<double>(c->poses_cand), (int64_t)c->NP * 12, c->stream);
     HIP_OK(hipGetLastError());
     HIP_OK(hipStreamSynchronize(c->stream));
@@ -1311,8 +1320,7 @@ pba_status pba_loss_forward(pba_ctx *c, const float *delta, int32_t on_device, d
     }
     // X = X0 boxplus delta (the step buffer is scratch here)
     launch_delta_to_dx(P_<float>(c->loss_delta), P_<double>(c->dx), N, c->stream);
-    launch_boxplus(P_<double>(c->poses), P_<double>(c->dx), nullptr, P_<double>(c->loss_poses), N, nullptr,
-                   nullptr, c->stream);
+    launch_boxplus(P_<double>(c->poses), P_<double>(c->dx), nullptr, P_<double>(c->loss_poses), N, c->stream);
     double *tot = P_<double>(c->totals) + 4;
     if ((s = run_eval(c, P_<double>(c->loss_poses), P_<double>(c->H_cand), P_<double>(c->b_cand), tot, false,
                       c->stream)))
@@ -1357,9 +1365,7 @@ pba_status pba_loss_backward(pba_ctx *c, double grad_F, float *grad_delta, float
     }
     // recompute the evaluation at X0 boxplus delta in adjoint mode
     const int ngrp = (int)c->groups.size();
-    launch_pair_setup(P_<double>(c->loss_poses), P_<int2>(c->pairs_d), c->P, P_<SensorDev>(c->L().sensors_d),
-                      P_<KfDev>(c->L().kfs_d), P_<PairDev>(c->pair_dev), P_<uint32_t>(c->counters), ngrp * kXcd,
-                      c->stream);
+    setup_pairs(c, P_<double>(c->loss_poses), PoseStep{}, P_<uint32_t>(c->counters), ngrp * kXcd, Stamp{}, c->stream);
     zbuffer_pass(c, P_<double>(c->loss_poses), c->stream, ctx_work(c));
     EvalArgs a = make_args(c);
     a.g_int = P_<float>(c->g_int);
@@ -1373,10 +1379,10 @@ pba_status pba_loss_backward(pba_ctx *c, double grad_F, float *grad_delta, float
     }
     HIP_OK(hipGetLastError());
     launch_reduce_pairs(c->partials.p, 1, P_<int32_t>(c->pitems), P_<int32_t>(c->ibeg), P_<int32_t>(c->icnt),
-                        P_<PairDev>(c->pair_dev), P_<double>(c->pair_out), c->P, c->stream);
+                        P_<PairDev>(c->pair_dev), P_<double>(c->pair_out), c->P, Stamp{}, c->stream);
     launch_assemble(P_<double>(c->pair_out), c->P, P_<int2>(c->blk_rc), P_<int32_t>(c->blk_ptr),
                     P_<int32_t>(c->blk_ent), c->nblk, P_<int32_t>(c->bk_ptr), P_<int32_t>(c->bk_ent), N,
-                    P_<double>(c->H_cand), P_<double>(c->b_cand), P_<double>(c->totals) + 4, c->stream);
+                    P_<double>(c->H_cand), P_<double>(c->b_cand), P_<double>(c->totals) + 4, nullptr, c->stream);
     launch_pose_grad(P_<double>(c->b_cand), P_<float>(c->loss_delta), grad_F, P_<float>(c->g_pose), N, c->stream);
     HIP_OK(hipGetLastError());
     const hipMemcpyKind kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
@@ -1678,8 +1684,7 @@ pba_status pba_debug_pair(pba_ctx *c, int32_t pair, uint8_t *status, float *uv, 
     if (pair < 0 || pair >= c->P) return fail(c, PBA_EINVAL, "pair %d out of range", pair);
     HIP_OK(hipSetDevice(c->cfg.device));
     // pair transforms at the current poses
-    launch_pair_setup(P_<double>(c->poses), P_<int2>(c->pairs_d), c->P, P_<SensorDev>(c->L().sensors_d),
-                      P_<KfDev>(c->L().kfs_d), P_<PairDev>(c->pair_dev), P_<uint32_t>(c->counters), 64, c->stream);
+    setup_pairs(c, P_<double>(c->poses), PoseStep{}, P_<uint32_t>(c->counters), 64, Stamp{}, c->stream);
     zbuffer_pass(c, P_<double>(c->poses), c->stream, ctx_work(c));
     int2 pr;
     HIP_OK(hipMemcpyAsync(&pr, P_<int2>(c->pairs_d) + pair, sizeof pr, hipMemcpyDeviceToHost, c->stream));
