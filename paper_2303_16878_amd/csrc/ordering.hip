@@ -196,16 +196,20 @@ NdArrays nd_arrays(const TilePattern &tp, const std::vector<int> &pos)
     }
     for (int l = 0; l < tp.nlev; ++l) {
         a.lbeg.push_back((int)a.lcols.size());
+        a.pbeg.push_back((int)a.panels.size() / 2);
         // target tile (a, b), b <= a -> the level's columns having both among their tile rows
         std::map<std::pair<int, int>, std::vector<int32_t>> tgt_of;
         for (int k = 0; k < nt; ++k) {
             if (tp.level[k] != l) continue;
             a.lcols.push_back(k);
             const std::vector<int> &r = tp.rows[k];
+            if (r.empty()) a.panels.insert(a.panels.end(), {k, -1});
+            for (int i : r) a.panels.insert(a.panels.end(), {k, i});
             for (size_t x = 0; x < r.size(); ++x)
                 for (size_t y = 0; y <= x; ++y) tgt_of[{r[x], r[y]}].push_back(k);
         }
         a.lcnt.push_back((int)a.lcols.size() - a.lbeg.back());
+        a.pcnt.push_back((int)a.panels.size() / 2 - a.pbeg.back());
         // the tasks with the most contributors first, so that they start early
         std::vector<std::pair<std::pair<int, int>, const std::vector<int32_t> *>> tl;
         for (const auto &t : tgt_of) tl.push_back({t.first, &t.second});

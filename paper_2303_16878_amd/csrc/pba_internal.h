@@ -205,7 +205,10 @@ void launch_fill(double *p, int64_t n, double v, hipStream_t st);
 
 // ---- launch wrappers (solve.hip)
 void launch_damp_copy(const double *H, const double *b, double *A, double *rhs, int n, int anchor,
-                      const LmState *lm, double lam_override, const Stamp &stamp, hipStream_t st);
+                      const LmState *lm, double lam_override, int32_t *fail, const Stamp &stamp, hipStream_t st);
+// A natural-order system of one block (n <= 64): damped, gauge-fixed, factored and solved into x in one launch.
+void launch_solve_small(const double *H, const double *b, int n, int anchor, const LmState *lm, double lam_override,
+                        double *x, int32_t *fail, const Stamp &stamp, hipStream_t st);
 struct CholPlan;
 // The same into the plan's nested-dissection order (plan.n rows, pattern tiles only); also
 // clears *fail.
@@ -235,6 +238,10 @@ struct CholPlan {
     int ndt = 0;
     const int32_t *lcols = nullptr;     // block columns grouped by level: level l at lcols + lbeg[l]
     std::vector<int> lbeg, lcnt;
+    // The factorisation's launches in either order, one panel and one update launch per level of the elimination
+    // tree (in the natural order of a chain, that is per block column):
+    const int32_t *panels = nullptr;    // 2 ints each: block column k, tile row a (-1 where k has none below)
+    std::vector<int> pbeg, pcnt;        // level l's panels at panels + 2 pbeg[l], columns together
     const int32_t *tasks = nullptr;     // update tasks, 4 ints each: target tile (a, b), first
     const int32_t *contrib = nullptr;   //   contributing column in contrib, count (ascending columns)
     std::vector<int> tbeg, tcnt;        // level l's tasks at tasks + 4 tbeg[l]
@@ -257,11 +264,11 @@ std::vector<std::vector<int>> nd_blocks(int nv, const std::vector<std::pair<int,
 // n_pad receives the padded order.
 std::vector<int> nd_positions(int nv, const std::vector<std::vector<int>> &blocks, int &n_pad);
 // The level-scheduled factorisation's lists for a pattern in a nested-dissection order (the
-// CholPlan fields of the same names, host side): perm, dtiles, lcols / lbeg / lcnt, and tasks /
-// contrib / tbeg / tcnt.
+// CholPlan fields of the same names, host side): perm, dtiles, lcols / lbeg / lcnt, panels / pbeg / pcnt, and
+// tasks / contrib / tbeg / tcnt.
 struct NdArrays {
-    std::vector<int32_t> perm, dtiles, lcols, tasks, contrib;
-    std::vector<int> lbeg, lcnt, tbeg, tcnt;
+    std::vector<int32_t> perm, dtiles, lcols, panels, tasks, contrib;
+    std::vector<int> lbeg, lcnt, pbeg, pcnt, tbeg, tcnt;
 };
 NdArrays nd_arrays(const TilePattern &tp, const std::vector<int> &pos);
 // A (n x n, lower triangle used) is overwritten; the factor's panel tiles go to L and, transposed,

@@ -83,7 +83,7 @@ struct pba_ctx {
     DevBuf poses, poses_cand, pairs_d, pair_dev, item_pair, item_px0, pitems, ibeg, icnt, counters, partials, pair_out;
     DevBuf blk_rc, blk_ptr, blk_ent, bk_ptr, bk_ent;
     DevBuf chol_rows, chol_cols, chol_meta;
-    DevBuf nd_perm, nd_off, nd_dtiles, nd_lcols, nd_tasks, nd_contrib, dx_nat;
+    DevBuf nd_perm, nd_off, nd_dtiles, nd_lcols, nd_panels, nd_tasks, nd_contrib, dx_nat;
     CholPlan chol;   // tiles of the Cholesky factor that can be nonzero
     DevBuf zbuf, zoff;   // z-buffer occlusion variant: per pair, one FP32 depth per target pixel
     int64_t zcells = 0;
@@ -385,34 +385,34 @@ pba_status build_chol_plan(pba_ctx *c, const std::vector<int32_t> &src, const st
     pl.np = np;
     pl.n = n;
     pl.nd = nd;
-    pl.lbeg.clear();
-    pl.lcnt.clear();
-    pl.tbeg.clear();
-    pl.tcnt.clear();
+    const NdArrays a = nd_arrays(tp, pos);
+    pl.lbeg = a.lbeg;
+    pl.lcnt = a.lcnt;
+    pl.pbeg = a.pbeg;
+    pl.pcnt = a.pcnt;
+    pl.tbeg = a.tbeg;
+    pl.tcnt = a.tcnt;
     pl.ndt = 0;
+    std::vector<int32_t> panels = a.panels, tasks = a.tasks, contrib = a.contrib;
+    contrib.push_back(0);   // keep the device arrays non-empty
+    tasks.insert(tasks.end(), {0, 0, 0, 0});
+    if ((s = upload(c, c->nd_panels, panels.data(), panels.size() * 4))) return s;
+    if ((s = upload(c, c->nd_tasks, tasks.data(), tasks.size() * 4))) return s;
+    if ((s = upload(c, c->nd_contrib, contrib.data(), contrib.size() * 4))) return s;
+    pl.panels = P_<int32_t>(c->nd_panels);
+    pl.tasks = P_<int32_t>(c->nd_tasks);
+    pl.contrib = P_<int32_t>(c->nd_contrib);
     if (nd) {
-        const NdArrays a = nd_arrays(tp, pos);
-        pl.lbeg = a.lbeg;
-        pl.lcnt = a.lcnt;
-        pl.tbeg = a.tbeg;
-        pl.tcnt = a.tcnt;
-        std::vector<int32_t> perm = a.perm, dtiles = a.dtiles, lcols = a.lcols, tasks = a.tasks, contrib = a.contrib;
-        pl.ndt = (int)dtiles.size() / 2;
-        contrib.push_back(0);
-        tasks.insert(tasks.end(), {0, 0, 0, 0});
-        if ((s = upload(c, c->nd_perm, perm.data(), perm.size() * 4))) return s;
+        pl.ndt = (int)a.dtiles.size() / 2;
+        if ((s = upload(c, c->nd_perm, a.perm.data(), a.perm.size() * 4))) return s;
         if ((s = upload(c, c->nd_off, pos.data(), pos.size() * 4))) return s;
-        if ((s = upload(c, c->nd_dtiles, dtiles.data(), dtiles.size() * 4))) return s;
-        if ((s = upload(c, c->nd_lcols, lcols.data(), lcols.size() * 4))) return s;
-        if ((s = upload(c, c->nd_tasks, tasks.data(), tasks.size() * 4))) return s;
-        if ((s = upload(c, c->nd_contrib, contrib.data(), contrib.size() * 4))) return s;
+        if ((s = upload(c, c->nd_dtiles, a.dtiles.data(), a.dtiles.size() * 4))) return s;
+        if ((s = upload(c, c->nd_lcols, a.lcols.data(), a.lcols.size() * 4))) return s;
         if ((s = ensure(c, c->dx_nat, (size_t)n0 * 8))) return s;
         pl.perm = P_<int32_t>(c->nd_perm);
         pl.pose_off = P_<int32_t>(c->nd_off);
         pl.dtiles = P_<int32_t>(c->nd_dtiles);
         pl.lcols = P_<int32_t>(c->nd_lcols);
-        pl.tasks = P_<int32_t>(c->nd_tasks);
-        pl.contrib = P_<int32_t>(c->nd_contrib);
     }
     // the factorisation's buffers at the factored order: working matrix, the factor's panels and
     // their transposes; the inverted diagonal blocks (64 x 64 each, zero-padded) then their
@@ -697,12 +697,17 @@ void enqueue_solve(pba_ctx *c, const LmState *lm, double lam_override, const Sta
     const CholPlan &pl = c->chol;
     const int n = pl.n;
     double *A = P_<double>(c->A), *Lf = A + (size_t)n * n, *LTf = Lf + (size_t)n * n;
+    if (!pl.nd && n <= 64) {
+        launch_solve_small(P_<double>(c->H), P_<double>(c->b), n, c->cfg.anchor, lm, lam_override, P_<double>(c->dx),
+                           P_<int32_t>(c->fail), stamp, st);
+        return;
+    }
     if (pl.nd)
         launch_damp_copy_perm(P_<double>(c->H), P_<double>(c->b), A, P_<double>(c->dx), n_sys(c), c->cfg.anchor, lm,
                               lam_override, pl, P_<int32_t>(c->fail), stamp, st);
     else
         launch_damp_copy(P_<double>(c->H), P_<double>(c->b), A, P_<double>(c->dx), n, c->cfg.anchor, lm,
-                         lam_override, stamp, st);
+                         lam_override, P_<int32_t>(c->fail), stamp, st);
     launch_cholesky(A, Lf, LTf, n, P_<double>(c->Winv), pl, P_<int32_t>(c->fail), st, P_<double>(c->dx));
     launch_chol_solve(Lf, LTf, P_<double>(c->Winv), P_<double>(c->dx), n, pl, P_<int32_t>(c->fail), st);
 }
@@ -877,7 +882,7 @@ pba_status pba_destroy(pba_ctx *c)
                       &c->fail, &c->logbuf, &c->dbg_status, &c->dbg_uv, &c->dbg_cell, &c->dbg_res,
                       &c->loss_delta, &c->loss_poses, &c->g_int, &c->g_dep, &c->g_nrm, &c->g_pose,
                       &c->chol_rows, &c->chol_cols, &c->chol_meta, &c->zbuf, &c->zoff, &c->nd_perm,
-                      &c->nd_off, &c->nd_dtiles, &c->nd_lcols, &c->nd_tasks, &c->nd_contrib, &c->dx_nat};
+                      &c->nd_off, &c->nd_dtiles, &c->nd_lcols, &c->nd_panels, &c->nd_tasks, &c->nd_contrib, &c->dx_nat};
     drop_graph(c);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     for (DevBuf *b : bufs) release(*b);

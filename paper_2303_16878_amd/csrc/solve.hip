@@ -13,13 +13,16 @@ namespace pba {
 
 constexpr int NB = 64;   // Cholesky block size
 
-// A = gauge-fixed H with Marquardt damping, rhs = -b (anchor rows zero).
+// A = gauge-fixed H with Marquardt damping, rhs = -b (anchor rows zero); also clears the failure flag.
 // lam_override >= 0 replaces the device-side lambda (direct solve calls).
 __global__ void damp_copy_kernel(const double *__restrict__ H, const double *__restrict__ b,
                                  double *__restrict__ A, double *__restrict__ rhs, int n, int anchor,
-                                 const LmState *lm, double lam_override, Stamp stamp)
+                                 const LmState *lm, double lam_override, int32_t *fail, Stamp stamp)
 {
-    if (blockIdx.x == 0 && threadIdx.x == 0) put_stamp(stamp, 2);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        put_stamp(stamp, 2);
+        *fail = 0;
+    }
     const double lam = lam_override >= 0.0 ? lam_override : lm->lam;
     const int a0 = 6 * anchor, a1 = a0 + 6;
     const int64_t nn = (int64_t)n * n;
@@ -76,28 +79,23 @@ void launch_damp_copy_perm(const double *H, const double *b, double *A, double *
 }
 
 void launch_damp_copy(const double *H, const double *b, double *A, double *rhs, int n, int anchor,
-                      const LmState *lm, double lam_override, const Stamp &stamp, hipStream_t st)
+                      const LmState *lm, double lam_override, int32_t *fail, const Stamp &stamp, hipStream_t st)
 {
     int64_t nn = (int64_t)n * n;
     int64_t blocks = (nn + 255) / 256;
     if (blocks > 8192) blocks = 8192;
     hipLaunchKernelGGL(damp_copy_kernel, dim3((unsigned)blocks), dim3(256), 0, st, H, b, A, rhs, n, anchor, lm,
-                       lam_override, stamp);
+                       lam_override, fail, stamp);
 }
 
-// ---- blocked right-looking Cholesky, lower triangle, A row-major n x n.
-// Per 64-wide block column: factor the diagonal block and invert its factor (one workgroup),
-// then, in one launch, form the panel below as X = B W^T with W = L_kk^-1 and update the
-// trailing lower triangle with it.  The panel tiles of the factor go to a second n x n matrix
-// (A itself keeps the input panel, which the same launch reads); the inverted diagonal blocks
-// are kept for the solves.
+// ---- blocked right-looking Cholesky, lower triangle, A row-major n x n, 64-wide block columns.
+// The columns of one level of the elimination tree of block columns go together, in two launches: one forms the
+// factor's panels X_ak = A_ak W_k^T, W_k = L_kk^-1 (a workgroup per panel tile, each factoring its column's
+// diagonal block for itself), the next subtracts X_a X_b^T from the tiles right of them.  A itself keeps the
+// panels' input; the panels go to L and, transposed, to LT, the inverted diagonal blocks to Winv for the solves.
+// 64-wide products run on the FP64 matrix cores.
 
-// The value of v in lane l (wave-uniform l), to every lane.
-__device__ __forceinline__ double bcast_lane(double v, int l)
-{
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
-                            __builtin_amdgcn_readlane(__double2loint(v), l));
-}
+typedef double d4 __attribute__((ext_vector_type(4)));
 
 // 1/sqrt(d) in FP64 to about an ulp: the hardware estimate refined by two Newton steps.
 __device__ __forceinline__ double rsqrt_f64(double d)
@@ -107,326 +105,336 @@ __device__ __forceinline__ double rsqrt_f64(double d)
     return y * fma(-0.5 * d * y, y, 1.5);
 }
 
-// Factor the diagonal block at k0 and write W = L_kk^-1 (lower, row-major 64 x 64, zero above the
-// diagonal) and W^T to Winv (blocks k0 / 64 and nblk + k0 / 64); the factor itself is not needed
-// (the panel and the solves use W).  One workgroup of 256 threads; a ragged last block is padded
-// with the identity, whose factor and inverse are the identity.
-//
-// Right-looking over single pivots, factor and inverse together, in registers: lane i of wave w
-// holds S(i, 16 w + jj), row i of the working copy S, and lane j of wave w holds V(16 w + jj, j),
-// column j of the working rows of the inverse (V = I initially), jj = 0..15.  At pivot k, with
-// p = S(k, k), c_i = S(i, k) for i > k and 0 otherwise, and r_j = V(k, j) (zero for j > k, r_k = 1:
-// V stays lower triangular), every element takes both
-//   S(i, j) -= c_i c_j / p,      V(i, j) -= c_i r_j / p
-// (c_j = 0 leaves S left of the pivot alone, r_j = 0 leaves V right of it alone), because
-// L(i, k) = c_i / sqrt(p) and row k of the inverse is V(k, :) / sqrt(p).  Column k of S is final
-// from then on, and V ends up holding W row-scaled by sqrt(p_i).  Both updates of a wave use the
-// same 16 values c_(16 w + jj), read from LDS as broadcasts, and one value per lane (c_i for S,
-// r_j for V).
-//
-// Pivots go four at a time per barrier: the wave owning columns k .. k + 3 of S (and rows
-// k .. k + 3 of V) factors that 64 x 4 panel on copies (cross-lane values by readlane), carries
-// the four rows of V along, and publishes the four columns c and rows r as they stand at their
-// pivots, with the pivots and their reciprocals; then every wave applies the four rank-one steps
-// in order.  No step branches on the lane or the wave.  (Broadcasting the 16 values by readlane
-// instead of LDS, skipping the column ranges a step cannot change, or eight pivots per barrier
-// all measured slower; keeping V with lane = row, which needs 32 readlanes per pivot, cost 30%.)
-//
-// kList: the launch factors the block columns cols[blockIdx.x] (one tree level of a nested-dissection
-// order; the failure flag was cleared before the factorisation), else the single block at k0, the
-// first of which (k0 = 0) clears the flag.  With x (kList only), the forward substitution's step
-// of the block rides along: x_k holds r_k, the right-hand side with every earlier column's
-// contribution already subtracted (by the update launches), and becomes y_k = W r_k.
-template <bool kList>
-__global__ void __launch_bounds__(256) chol_diag_kernel(const double *A, int n, int k0_arg,
-                                                        const int32_t *__restrict__ cols, double *Winv,
-                                                        int32_t *fail, double *x)
+// x of lane K of each 16-lane row, in every lane of the row (one 64-bit DPP move).
+template <int K>
+__device__ __forceinline__ double row_bcast(double x)
 {
-    __shared__ double cb[2][4][NB];   // the four columns c of a pivot group (double-buffered)
-    __shared__ double rb[2][4][NB];   // the four rows r of V at their pivots
-    __shared__ double pb[2][4];       // the pivots
-    __shared__ double qb[2][4];       // their reciprocals
-    __shared__ double piv[NB];
-    __shared__ double Ts[NB][NB + 1];   // W, transposed on the way out
-    const int k0 = kList ? cols[blockIdx.x] * NB : k0_arg;
-    const bool clears = !kList && k0 == 0;
-    if (!clears && *fail) return;
-    const int nb = min(NB, n - k0);
-    const int lane = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int c0 = 16 * w;
-    double a[16], v[16];   // S(lane, c0 + jj), V(c0 + jj, lane)
-#pragma unroll
-    for (int jj = 0; jj < 16; ++jj) {
-        const int j = c0 + jj;
-        a[jj] = (lane < nb && j < nb) ? A[(int64_t)(k0 + lane) * n + k0 + j] : (lane == j ? 1.0 : 0.0);
-        v[jj] = lane == j ? 1.0 : 0.0;
+    return __builtin_amdgcn_update_dpp(0.0, x, 0x150 + K, 0xF, 0xF, true);
+}
+
+// c += P Q over 16 k-steps-of-four: operand lane l holds P[l % 16][4 s + l / 16] and Q[4 s + l / 16][l % 16]; element
+// c[r] of lane l is row 4 r + l / 16, column l % 16.
+__device__ __forceinline__ d4 mma(double p, double q, d4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(p, q, c, 0, 0, 0); }
+
+// x += (x of lane K of the 16-lane row) * g, one instruction.  The DPP operand must not have been written by the two
+// vector instructions before (the leading s_nop), nor may the two after read the result by DPP.
+template <int K>
+__device__ __forceinline__ void fmac_bcast(double &x, double g)
+{
+    asm volatile("s_nop 1\n\tv_fmac_f64_dpp %0, %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf\n\ts_nop 1" : "+v"(x) : "v"(g), "n"(K));
+}
+// The same for seven values.
+template <int K>
+__device__ __forceinline__ void fmac_bcast(double &x0, double &x1, double &x2, double &x3, double &x4, double &x5, double &x6, double g)
+{
+    asm volatile("s_nop 1\n\t"
+                 "v_fmac_f64_dpp %0, %0, %7 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %1, %1, %7 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %2, %2, %7 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %3, %3, %7 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %4, %4, %7 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %5, %5, %7 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %6, %6, %7 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+                 "s_nop 1"
+                 : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3), "+v"(x4), "+v"(x5), "+v"(x6) : "v"(g), "n"(K));
+}
+
+// Pivots K .. 15 of the 16 x 16 factor-and-invert below.  The next pivot's column is updated first and its
+// reciprocal started before the other 14, so the chain from pivot to pivot overlaps them.
+template <int K>
+__device__ __forceinline__ void pivots16(double (&a)[16], int r, double p, double q, double &pown, bool &bad)
+{
+    const bool ok = p > 0.0;
+    bad = bad || !ok;
+    q = fma(q, fma(-p, q, 1.0), q);
+    q = fma(q, fma(-p, q, 1.0), q);
+    const bool below = r > K;
+    const double g = below && ok ? -a[K] * q : 0.0;
+    pown = r == K && ok ? p : pown;
+    // (a[K] itself becomes g below the pivot; its old value is not needed any more)
+#define PBA_COL(d) a[(K + d) & 15]
+    fmac_bcast<K>(PBA_COL(1), g);
+    double pn = 1.0, qn = 1.0;
+    if constexpr (K < 15) {
+        pn = row_bcast<K + 1>(a[K + 1]);
+        qn = __builtin_amdgcn_rcp(pn);
+        __builtin_amdgcn_sched_barrier(0);
     }
+    fmac_bcast<K>(PBA_COL(2), PBA_COL(3), PBA_COL(4), PBA_COL(5), PBA_COL(6), PBA_COL(7), PBA_COL(8), g);
+    fmac_bcast<K>(PBA_COL(9), PBA_COL(10), PBA_COL(11), PBA_COL(12), PBA_COL(13), PBA_COL(14), PBA_COL(15), g);
+#undef PBA_COL
+    a[K] = below ? g : a[K];
+    if constexpr (K < 15) pivots16<K + 1>(a, r, pn, qn, pown, bad);
+}
+
+constexpr int kLd = NB + 1;   // LDS row pitch of a 64-wide tile (odd: rows 16 apart fall in distinct banks)
+struct FactorLds {
+    double X[NB - 16][17];    // the block column's factor below the diagonal block
+    double Wd[16][17];        // the diagonal block's inverse factor
+};
+
+// W = L^-1 for the 64 x 64 symmetric matrix M = L L^T, in place in M's lower triangle (strictly upper 16 x 16
+// blocks are left as they are; the upper part of the diagonal ones becomes zero).  Only M's lower blocks and the
+// whole of its diagonal 16 x 16 blocks are read.  256 threads; false where a pivot is not positive.
+//
+// Block Gauss-Jordan over four 16-wide block columns.  Every wave factors and inverts the diagonal block for
+// itself: lane l holds row l % 16 (the four 16-lane rows alike), pivot k subtracts row k times c_i / p from the
+// rows below, where columns right of k are the remaining matrix and columns left of it already rows of the inverse
+// (column k itself becomes the new one, -c_i / p), so one update of 15 values serves both; a pivot row's
+// values reach the lanes by DPP, no LDS, no barrier.  W's rows are those, scaled by 1 / sqrt(p_i).  Then each wave
+// forms one block: X_w = M_w,k W_k^T below, R_w = W_k M_k,w left of the diagonal; and the blocks below take
+// M_it -= X_i X_t^T (t > k), M_it -= X_i R_t (t < k), M_ik = -X_i W_k; two barriers per block column.  A latency
+// chain: 16 pivots take 3300 cycles (the reciprocal and its refinement, 200 each), a block column's products 2200 on
+// average; 10.7 us a tile, and about 5 more while the launch's instructions come from memory.  64 single pivots
+// exchanged through LDS took 700 cycles each (20 us); a DPP move and an FMA per value 450 (the move's latency).
+__device__ __forceinline__ bool factor64(double (*M)[kLd], FactorLds &F)
+{
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = l & 15, q = l >> 4;
     bool bad = false;
 #pragma unroll 1
-    for (int wo = 0; wo < 4; ++wo) {
+    for (int kb = 0; kb < 4; ++kb) {
+        const int d0 = 16 * kb;
+        double a[16], pown = 1.0, m[4];
 #pragma unroll
-        for (int tb = 0; tb < 4; ++tb) {
-            const int kb = 4 * tb, k = 16 * wo + kb, b = tb & 1;
-            if (w == wo) {
-                double t[4], r[4];
+        for (int j = 0; j < 16; ++j) a[j] = M[d0 + r][d0 + j];
+        // the wave's own block of phase 1 (M_w,k below the diagonal block, M_k,w left of it), ahead of the pivots
+        {
+            const double *mb = w > kb ? &M[16 * w + r][d0 + q] : &M[d0 + q][16 * w + r];
+            const int step = w > kb ? 4 : 4 * kLd;
 #pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    t[m] = a[kb + m];
-                    r[m] = v[kb + m];
-                }
-#pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    const double p = bcast_lane(t[m], k + m);
-                    double q = __builtin_amdgcn_rcp(p);
-                    q = fma(q, fma(-p, q, 1.0), q);
-                    q = fma(q, fma(-p, q, 1.0), q);
-                    const double c = lane > k + m ? t[m] : 0.0;
-                    cb[b][m][lane] = c;
-                    rb[b][m][lane] = r[m];
-                    if (lane == 0) {
-                        pb[b][m] = p;
-                        qb[b][m] = q;
-                    }
-#pragma unroll
-                    for (int m2 = m + 1; m2 < 4; ++m2) {
-                        const double cm2 = bcast_lane(t[m], k + m2);
-                        t[m2] = fma(-c * q, cm2, t[m2]);
-                        r[m2] = fma(-cm2 * q, r[m], r[m2]);
-                    }
-                }
-            }
-            __syncthreads();
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                const double p = pb[b][m];
-                const bool ok = p > 0.0;
-                bad = bad || !ok;
-                if (threadIdx.x == 0) piv[k + m] = ok ? p : 1.0;
-                const double qq = ok ? qb[b][m] : 0.0;
-                const double cr = -cb[b][m][lane] * qq, rr = -rb[b][m][lane] * qq;
-#pragma unroll
-                for (int jj = 0; jj < 16; ++jj) {
-                    const double cj = cb[b][m][c0 + jj];
-                    a[jj] = fma(cr, cj, a[jj]);
-                    v[jj] = fma(rr, cj, v[jj]);
-                }
-            }
+            for (int s = 0; s < 4; ++s) m[s] = mb[s * step];
         }
-    }
-    __syncthreads();
-    double *Wb = Winv + (int64_t)(k0 / NB) * NB * NB;
-    double *Wtb = Winv + (int64_t)((n + NB - 1) / NB + k0 / NB) * NB * NB;
+        const double p0 = row_bcast<0>(a[0]);
+        pivots16<0>(a, r, p0, __builtin_amdgcn_rcp(p0), pown, bad);
+        const double rs = rsqrt_f64(pown);
+        // W_k's rows before scaling as an operand: row l % 16, columns 4 s + l / 16
+        double v[4];
 #pragma unroll
-    for (int jj = 0; jj < 16; ++jj) {
-        const int i = c0 + jj;
-        const double sp = rsqrt_f64(piv[i]);
-        const bool low = lane <= i, in = i < nb && lane < nb;
-        const double wv = (low && in) ? v[jj] * sp : 0.0;
-        Wb[i * NB + lane] = wv;
-        Ts[lane][i] = wv;
-    }
-    __syncthreads();
+        for (int s = 0; s < 4; ++s) {
+            const double t = q < 2 ? (q == 0 ? a[4 * s] : a[4 * s + 1]) : (q == 2 ? a[4 * s + 2] : a[4 * s + 3]);
+            v[s] = 4 * s + q < r ? t : (4 * s + q == r ? 1.0 : 0.0);
+        }
+        d4 c = {0.0, 0.0, 0.0, 0.0};
+        if (w > kb) {   // X's column l % 16 is scaled by that row's factor, which this lane has
 #pragma unroll
-    for (int jj = 0; jj < 16; ++jj) Wtb[(c0 + jj) * NB + lane] = Ts[c0 + jj][lane];
-    if (threadIdx.x == 0 && (bad || clears)) *fail = bad ? 1 : 0;
-    if (kList && x) {   // y_k = W r_k: row i = t / 4, columns 16 (t % 4) .. +15 (Ts[j][i] = W(i, j))
-        double *rk = x + k0;
-        if (threadIdx.x < NB) piv[threadIdx.x] = rk[threadIdx.x];   // r_k (the pivots are no longer needed)
+            for (int s = 0; s < 4; ++s) c = mma(m[s], v[s], c);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) F.X[16 * (w - kb - 1) + 4 * e + q][r] = c[e] * rs;
+        } else if (w < kb) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) c = mma(v[s] * rs, m[s], c);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) M[d0 + 4 * e + q][16 * w + r] = c[e];
+        } else {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) F.Wd[r][4 * s + q] = v[s] * rs;
+        }
         __syncthreads();
-        const int i = threadIdx.x >> 2, j0 = (threadIdx.x & 3) * 16;
-        double y = 0.0;
+        // phase 2: block b of the list (i, t), i = kb + 1 .. 3, t = 0 .. i, to wave b % 4; the operands of a wave's
+        // next block are read while one is multiplied
+        const int nb2 = kb == 0 ? 9 : kb == 1 ? 7 : kb == 2 ? 4 : 0;
+        auto locate = [&](int b, int &i, int &t) {
+            i = kb + 1;
+            while (b > i) { b -= i + 1; ++i; }
+            t = b;
+        };
+        struct Ops { d4 v; double x[4], y[4]; };
+        auto read = [&](int b, Ops &o) {
+            int i, t;
+            locate(b, i, t);
+            const double *xb = &F.X[16 * (i - kb - 1) + r][q];
+            const double *yb = t > kb ? &F.X[16 * (t - kb - 1) + r][q] : t == kb ? &F.Wd[q][r] : &M[d0 + q][16 * t + r];
+            const int ys = t > kb ? 4 : t == kb ? 4 * 17 : 4 * kLd;
 #pragma unroll
-        for (int j = 0; j < 16; ++j) y = fma(Ts[j0 + j][i], piv[j0 + j], y);
-        y += __shfl_xor(y, 1, 64);
-        y += __shfl_xor(y, 2, 64);
-        if ((threadIdx.x & 3) == 0) rk[i] = y;
-    }
-}
-
-// C += P Q^T over k = 0..63 for tiles in LDS (rows padded to 65 doubles), 16 x 16 threads,
-// RA x RB outputs each: rows ty + 16 a of P, rows tx + 16 b of Q.  With the odd row pitch the 16
-// rows a wave reads from Q fall in distinct banks (rows 4 tx + b would collide four ways).
-template <int RA, int RB>
-__device__ __forceinline__ void tile_nt(const double (*P)[NB + 1], const double (*Q)[NB + 1], int tx, int ty,
-                                        double (&c)[RA][RB])
-{
-#pragma unroll 32
-    for (int k = 0; k < NB; ++k) {
-        double p[RA], q[RB];
+            for (int s = 0; s < 4; ++s) { o.x[s] = xb[4 * s]; o.y[s] = yb[s * ys]; }
 #pragma unroll
-        for (int a = 0; a < RA; ++a) p[a] = P[ty + 16 * a][k];
+            for (int e = 0; e < 4; ++e) o.v[e] = t == kb ? 0.0 : M[16 * i + 4 * e + q][16 * t + r];
+        };
+        auto multiply = [&](int b, Ops &o) {
+            int i, t;
+            locate(b, i, t);
 #pragma unroll
-        for (int b = 0; b < RB; ++b) q[b] = Q[tx + 16 * b][k];
+            for (int s = 0; s < 4; ++s) o.v = mma(-o.x[s], o.y[s], o.v);
 #pragma unroll
-        for (int a = 0; a < RA; ++a)
-#pragma unroll
-            for (int b = 0; b < RB; ++b) c[a][b] = fma(p[a], q[b], c[a][b]);
-    }
-}
-
-// Rows r0 .. r0 + R - 1 (those below `rows`), columns c0 .. c0 + nc - 1 of the row-major matrix M
-// (row pitch ld, even; c0 and nc even) into a zero-padded R x 64 LDS tile, by a 256-thread
-// workgroup.  All of a thread's 16-byte loads are issued before the first is used.
-template <int R>
-__device__ __forceinline__ void load_tile(double (*T)[NB + 1], const double *M, int64_t ld, int rows, int r0,
-                                          int c0, int nc)
-{
-    constexpr int kIt = R * NB / 2 / 256;
-    double2 v[kIt];
-#pragma unroll
-    for (int it = 0; it < kIt; ++it) {
-        const int e = it * 256 + (int)threadIdx.x, i = e >> 5, k = (e & 31) * 2;
-        v[it] = (r0 + i < rows && k < nc) ? *reinterpret_cast<const double2 *>(M + (r0 + i) * ld + c0 + k)
-                                          : make_double2(0.0, 0.0);
-    }
-#pragma unroll
-    for (int it = 0; it < kIt; ++it) {
-        const int e = it * 256 + (int)threadIdx.x, i = e >> 5, k = (e & 31) * 2;
-        T[i][k] = v[it].x;
-        T[i][k + 1] = v[it].y;
-    }
-}
-
-// Panel and trailing update of block column k0 in one launch, four workgroups per pair (bi, bj),
-// bi >= bj, of the column's tile rows (ascending list `tiles`).  Workgroup (pair, qi, qj) takes
-// rows 32 qi .. 32 qi + 31 of tile row bi and rows 32 qj .. 32 qj + 31 of tile row bj: it forms
-// those rows of the panel, X = B W^T, from the input panel B in A, then applies A_ij -= X_i X_j^T
-// to its 32 x 32 quarter of tile (bi, bj).  On the diagonal pairs the quarter above the diagonal
-// has nothing to do, and the workgroups with qj = 0 write their rows of X_i to L and L^T.  Panel rows are
-// recomputed by the workgroups that need them, so no workgroup waits for another.
-__global__ void __launch_bounds__(256) chol_panel_update_kernel(double *A, double *L, double *LT, int n, int k0,
-                                                                const double *__restrict__ Winv,
-                                                                const int32_t *__restrict__ tiles,
-                                                                const int32_t *fail)
-{
-    constexpr int H = NB / 2;
-    __shared__ double Ws[NB][NB + 1];
-    __shared__ double Xi[H][NB + 1];
-    __shared__ double Xj[H][NB + 1];
-    if (*fail) return;
-    const int nb = min(NB, n - k0);
-    const int idx = blockIdx.x >> 2, qi = (blockIdx.x >> 1) & 1, qj = blockIdx.x & 1;
-    int bi = (int)((sqrt(8.0 * idx + 1.0) - 1.0) * 0.5);
-    while ((bi + 1) * (bi + 2) / 2 <= idx) ++bi;
-    while (bi * (bi + 1) / 2 > idx) --bi;
-    const int bj = idx - bi * (bi + 1) / 2;
-    const bool diag = bi == bj;
-    const int ri = tiles[bi] * NB + H * qi, rj = tiles[bj] * NB + H * qj;
-    const int ni = min(H, n - ri), nj = min(H, n - rj);
-    if ((diag && qj > qi) || ni <= 0 || nj <= 0) return;   // uniform over the workgroup
-    const bool same = diag && qi == qj;                      // X_j rows are X_i's
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    load_tile<NB>(Ws, Winv + (int64_t)(k0 / NB) * NB * NB, NB, NB, 0, 0, NB);
-    load_tile<H>(Xi, A, n, n, ri, k0, nb);
-    if (!same) load_tile<H>(Xj, A, n, n, rj, k0, nb);
-    __syncthreads();
-    // X = B W^T in place: the results stay in registers until every thread has read B
-    double ci[2][4] = {}, cj[2][4] = {};
-    tile_nt(Xi, Ws, tx, ty, ci);
-    if (!same) tile_nt(Xj, Ws, tx, ty, cj);
-    __syncthreads();
-    const bool write_l = diag && qj == 0;
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int i = ty + 16 * a, j = tx + 16 * q;
-            Xi[i][j] = ci[a][q];
-            if (!same) Xj[i][j] = cj[a][q];
-            if (write_l && i < ni && j < nb) L[(int64_t)(ri + i) * n + k0 + j] = ci[a][q];
+            for (int e = 0; e < 4; ++e) M[16 * i + 4 * e + q][16 * t + r] = o.v[e];
+        };
+        if (w < nb2) {
+            Ops o0, o1;
+            read(w, o0);
+            if (w + 4 < nb2) read(w + 4, o1);
+            multiply(w, o0);
+            if (w + 8 < nb2) read(w + 8, o0);
+            if (w + 4 < nb2) multiply(w + 4, o1);
+            if (w + 8 < nb2) multiply(w + 8, o0);
         }
-    __syncthreads();
-    if (write_l)   // the same rows into L^T, read back column-wise so the stores run along its rows
-        for (int e = tid; e < H * NB; e += 256) {
-            const int i = e % H, j = e / H;
-            if (i < ni && j < nb) LT[(int64_t)(k0 + j) * n + ri + i] = Xi[i][j];
-        }
-    double c[2][2] = {};
-    tile_nt(Xi, same ? Xi : Xj, tx, ty, c);
+        if (w == kb)   // W_k in its place
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int i = ty + 16 * a, j = tx + 16 * q;
-            if (i < ni && j < nj && (!diag || H * qj + j <= H * qi + i)) A[(int64_t)(ri + i) * n + rj + j] -= c[a][q];
-        }
+            for (int s = 0; s < 4; ++s) M[d0 + r][d0 + 4 * s + q] = v[s] * rs;
+        __syncthreads();
+    }
+    return !bad;
 }
 
-// One elimination-tree level of a nested-dissection factorisation, after its diagonal blocks: every
-// block column k of the level contributes A_ab -= X_a X_b^T, X = A_(., k) W_k^T, to the tiles (a, b),
-// b <= a, of its tile rows, and writes X as its panel of the factor.  The tiles a level writes
-// belong to higher levels, so no tile is both read as a panel and updated here.  One task per
-// target tile lists its contributing columns (ascending); workgroup (task, qi, qj) owns one
-// 32 x 32 quarter of the target and sums the contributions in registers, column by column in
-// that order, before subtracting them: the result does not depend on the schedule.  The
-// workgroups of a diagonal target with qj = 0 write their rows of each contributor's panel to L
-// and L^T.
-//
-// The forward substitution rides along: the diagonal targets' workgroups, which form each
-// contributor's panel rows X_a = L_ak anyway, subtract L_ak y_k from their rows r_a of x (y_k was
-// written by this level's diagonal launch; r_a belongs to a higher level and only this task
-// writes it).
-__global__ void __launch_bounds__(256) chol_level_update_kernel(double *A, double *L, double *LT, int n,
-                                                                const double *__restrict__ Winv,
-                                                                const int32_t *__restrict__ tasks,
-                                                                const int32_t *__restrict__ contrib,
-                                                                const int32_t *fail, double *x)
+// The diagonal tile at k0 (nb rows) into M, its upper part mirrored from the lower (which alone is kept up to date),
+// padded with the identity.
+__device__ __forceinline__ void load_diag(double (*M)[kLd], const double *A, int64_t n, int k0, int nb)
 {
-    constexpr int H = NB / 2;
-    __shared__ double Ws[NB][NB + 1];
-    __shared__ double Xi[H][NB + 1];
-    __shared__ double Xj[H][NB + 1];
+    double v[NB * NB / 256];
+#pragma unroll
+    for (int it = 0; it < NB * NB / 256; ++it) {
+        const int e = it * 256 + (int)threadIdx.x, i = e >> 6, j = e & 63;
+        v[it] = (j <= i && i < nb) ? A[(int64_t)(k0 + i) * n + k0 + j] : (i == j ? 1.0 : 0.0);
+    }
+#pragma unroll
+    for (int it = 0; it < NB * NB / 256; ++it) {
+        const int e = it * 256 + (int)threadIdx.x, i = e >> 6, j = e & 63;
+        if (j <= i) { M[i][j] = v[it]; M[j][i] = v[it]; }
+    }
+}
+
+// Panels of one level: workgroup = entry (k, a) of `panels`, column k's diagonal block and its tile row a (a < 0: a
+// column without rows below).  Every workgroup of a column factors the diagonal block for itself (bitwise alike),
+// so no workgroup waits for another; the column's first one writes W and W^T and, with x, the forward
+// substitution's y_k = W r_k (x_k holds r_k, from which every earlier column's part has been subtracted).
+// Latency-bound: 21 us a launch, of which the factor takes 16 and the panel's products 2 (lidar64's eight levels:
+// diagonal blocks 24 us and updates that formed the panels from LDS 14 to 53 us; now 21 and 5 to 11).
+__global__ void __launch_bounds__(256) chol_panel_kernel(const double *__restrict__ A, double *__restrict__ L,
+                                                         double *__restrict__ LT, int n,
+                                                         const int2 *__restrict__ panels, double *__restrict__ Winv,
+                                                         int32_t *fail, double *x)
+{
+    __shared__ double M[NB][kLd], T[NB][kLd];
+    __shared__ FactorLds F;
+    // (no early return on a failure: this launch sets the flag itself, so its waves could disagree)
+    const int2 ka = panels[blockIdx.x];
+    const bool first = blockIdx.x == 0 || panels[(int)blockIdx.x - 1].x != ka.x;
+    const int k0 = ka.x * NB, ra = ka.y * NB, nb = min(NB, n - k0), tid = threadIdx.x;
+    const int l = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), r = l & 15, q = l >> 4;
+    // the panel tile's input is fetched ahead of the factorisation (its columns are whole: only the last block
+    // column can be ragged, and that has no rows below)
+    double2 t[NB * NB / 512];
+#pragma unroll
+    for (int it = 0; it < NB * NB / 512; ++it) {
+        const int e = it * 256 + tid, i = e >> 5, j = (e & 31) * 2;
+        t[it] = ka.y >= 0 && ra + i < n ? *reinterpret_cast<const double2 *>(A + (int64_t)(ra + i) * n + k0 + j)
+                                        : make_double2(0.0, 0.0);
+    }
+    load_diag(M, A, n, k0, nb);
+    __syncthreads();
+    if (!factor64(M, F) && first && tid == 0) *fail = 1;
+    if (first) {
+        double *Wb = Winv + (int64_t)ka.x * NB * NB, *Wtb = Wb + (int64_t)((n + NB - 1) / NB) * NB * NB;
+#pragma unroll
+        for (int it = 0; it < NB * NB / 256; ++it) {
+            const int e = it * 256 + tid, i = e >> 6, j = e & 63;
+            Wb[e] = j <= i && i < nb ? M[i][j] : 0.0;
+            Wtb[e] = i <= j && j < nb ? M[j][i] : 0.0;
+        }
+        if (x) {   // rows i = tid / 4, columns 16 (tid % 4) .. +15
+            const int i = tid >> 2, j0 = (tid & 3) * 16;
+            double y = 0.0;
+#pragma unroll
+            for (int j = 0; j < 16; ++j)
+                if (j0 + j <= i) y = fma(M[i][j0 + j], x[k0 + j0 + j], y);
+            y += __shfl_xor(y, 1, 64);
+            y += __shfl_xor(y, 2, 64);
+            __syncthreads();   // every r_k read (x has whole blocks)
+            if ((tid & 3) == 0) x[k0 + i] = y;
+        }
+    }
+    if (ka.y < 0) return;   // uniform over the workgroup
+#pragma unroll
+    for (int it = 0; it < NB * NB / 512; ++it) {
+        const int e = it * 256 + tid, i = e >> 5, j = (e & 31) * 2;
+        T[i][j] = t[it].x;
+        T[i][j + 1] = t[it].y;
+    }
+    __syncthreads();
+    // X = A_ak W^T: wave w rows 16 w .. +15 (it alone reads and writes them); W is lower triangular
+    double p[16];
+#pragma unroll
+    for (int s = 0; s < 16; ++s) p[s] = T[16 * w + r][4 * s + q];
+#pragma unroll
+    for (int jb = 0; jb < 4; ++jb) {
+        d4 c = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int s = 0; s < 4 * (jb + 1); ++s) c = mma(p[s], M[16 * jb + r][4 * s + q], c);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int i = 16 * w + 4 * e + q, j = 16 * jb + r;
+            T[i][j] = c[e];
+            if (ra + i < n) L[(int64_t)(ra + i) * n + k0 + j] = c[e];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < NB * NB / 256; ++it) {   // L^T, read back column-wise so the stores run along its rows
+        const int e = it * 256 + tid, j = e >> 6, i = e & 63;
+        if (ra + i < n) LT[(int64_t)(k0 + j) * n + ra + i] = T[i][j];
+    }
+}
+
+// Updates of one level after its panels: every block column k of the level contributes A_ab -= X_a X_b^T to the
+// tiles (a, b), b <= a, of its tile rows.  They belong to higher levels, so nothing this level reads is written.  One
+// task per target tile lists its contributing columns (ascending); workgroup (task, qi, qj) owns one 32 x 32
+// quarter, a 16 x 16 block of it per wave, and sums the contributions in that order before subtracting them, so
+// the result does not depend on the schedule.  The next contributor's rows are fetched while one is multiplied.
+// With x, the diagonal targets' workgroups with qj = 0 subtract L_ak y_k from their rows of x (the forward
+// substitution; y_k was written by this level's panels, and only this task writes those rows).
+__global__ void __launch_bounds__(256) chol_update_kernel(double *A, const double *__restrict__ L, int n,
+                                                          const int32_t *__restrict__ tasks,
+                                                          const int32_t *__restrict__ contrib, const int32_t *fail,
+                                                          double *x)
+{
+    constexpr int H = NB / 2, kIt = H * NB / 512;
+    __shared__ double Xi[H][kLd], Xj[H][kLd];
     if (*fail) return;
     const int4 tk = reinterpret_cast<const int4 *>(tasks)[blockIdx.x >> 2];
     const int qi = (blockIdx.x >> 1) & 1, qj = blockIdx.x & 1;
     const bool diag = tk.x == tk.y;
-    if (diag && qj > qi) return;   // uniform over the workgroup
-    const bool same = diag && qi == qj, write_l = diag && qj == 0;
     const int ri = tk.x * NB + H * qi, rj = tk.y * NB + H * qj;
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    double c[2][2] = {};
-    double z = 0.0;   // write_l: sum over the contributors of L_ak y_k, row tid / 8 of the quarter
+    if ((diag && qj > qi) || ri >= n) return;   // uniform over the workgroup
+    const bool fwd = diag && qj == 0 && x;
+    const int tid = threadIdx.x, l = tid & 63, w = tid >> 6, r = l & 15, q = l >> 4;
+    const int bi = 16 * (w >> 1), bj = 16 * (w & 1);
+    double2 ti[kIt], tj[kIt];
+    auto fetch = [&](int e) {
+        const int k0 = contrib[tk.z + e] * NB;
+#pragma unroll
+        for (int it = 0; it < kIt; ++it) {
+            const int o = it * 256 + tid, i = o >> 5, k = (o & 31) * 2;
+            ti[it] = ri + i < n ? *reinterpret_cast<const double2 *>(L + (int64_t)(ri + i) * n + k0 + k) : make_double2(0.0, 0.0);
+            tj[it] = rj + i < n ? *reinterpret_cast<const double2 *>(L + (int64_t)(rj + i) * n + k0 + k) : make_double2(0.0, 0.0);
+        }
+    };
+    d4 c = {0.0, 0.0, 0.0, 0.0};
+    double z = 0.0;   // fwd: sum over the contributors of L_ak y_k, row tid / 8 of the quarter
+    fetch(0);
     for (int e = 0; e < tk.w; ++e) {
-        const int kb = contrib[tk.z + e], k0 = kb * NB;
-        load_tile<NB>(Ws, Winv + (int64_t)kb * NB * NB, NB, NB, 0, 0, NB);
-        load_tile<H>(Xi, A, n, n, ri, k0, NB);
-        if (!same) load_tile<H>(Xj, A, n, n, rj, k0, NB);
-        __syncthreads();
-        double ci[2][4] = {}, cj[2][4] = {};
-        tile_nt(Xi, Ws, tx, ty, ci);
-        if (!same) tile_nt(Xj, Ws, tx, ty, cj);
+#pragma unroll
+        for (int it = 0; it < kIt; ++it) {
+            const int o = it * 256 + tid, i = o >> 5, k = (o & 31) * 2;
+            Xi[i][k] = ti[it].x; Xi[i][k + 1] = ti[it].y;
+            Xj[i][k] = tj[it].x; Xj[i][k + 1] = tj[it].y;
+        }
+        if (e + 1 < tk.w) fetch(e + 1);
         __syncthreads();
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int i = ty + 16 * a, j = tx + 16 * q;
-                Xi[i][j] = ci[a][q];
-                if (!same) Xj[i][j] = cj[a][q];
-                if (write_l) L[(int64_t)(ri + i) * n + k0 + j] = ci[a][q];
-            }
-        __syncthreads();
-        if (write_l) {
-            for (int e2 = tid; e2 < H * NB; e2 += 256) {
-                const int i = e2 % H, j = e2 / H;
-                LT[(int64_t)(k0 + j) * n + ri + i] = Xi[i][j];
-            }
-            const int i = tid >> 3, j0 = (tid & 7) * 8;   // 8 lanes per row, 8 columns each
+        for (int s = 0; s < 16; ++s) c = mma(Xi[bi + r][4 * s + q], Xj[bj + r][4 * s + q], c);
+        if (fwd) {
+            const int i = tid >> 3, j0 = (tid & 7) * 8, k0 = contrib[tk.z + e] * NB;   // 8 lanes per row, 8 columns each
 #pragma unroll
             for (int j = 0; j < 8; ++j) z = fma(Xi[i][j0 + j], x[k0 + j0 + j], z);
         }
-        tile_nt(Xi, same ? Xi : Xj, tx, ty, c);
-        __syncthreads();   // the next contributor's tiles overwrite the LDS
+        __syncthreads();
     }
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int i = ty + 16 * a, j = tx + 16 * q;
-            if (!diag || H * qj + j <= H * qi + i) A[(int64_t)(ri + i) * n + rj + j] -= c[a][q];
-        }
-    if (write_l && x) {   // uniform over the workgroup
+    for (int e = 0; e < 4; ++e) {
+        const int i = bi + 4 * e + q, j = bj + r;
+        if (ri + i < n && rj + j < n && (!diag || H * qj + j <= H * qi + i)) A[(int64_t)(ri + i) * n + rj + j] -= c[e];
+    }
+    if (fwd) {
         z += __shfl_xor(z, 1, 64);
         z += __shfl_xor(z, 2, 64);
         z += __shfl_xor(z, 4, 64);
@@ -437,26 +445,64 @@ __global__ void __launch_bounds__(256) chol_level_update_kernel(double *A, doubl
 void launch_cholesky(double *A, double *L, double *LT, int n, double *Winv, const CholPlan &plan, int32_t *fail,
                      hipStream_t st, double *x)
 {
-    if (plan.nd) {
-        for (size_t l = 0; l < plan.lcnt.size(); ++l) {
-            hipLaunchKernelGGL(chol_diag_kernel<true>, dim3(plan.lcnt[l]), dim3(256), 0, st, A, n, 0,
-                               plan.lcols + plan.lbeg[l], Winv, fail, x);
-            if (plan.tcnt[l] > 0)
-                hipLaunchKernelGGL(chol_level_update_kernel, dim3(4 * plan.tcnt[l]), dim3(256), 0, st, A, L, LT, n,
-                                   Winv, plan.tasks + 4 * (int64_t)plan.tbeg[l], plan.contrib, fail, x);
-        }
-        return;
+    for (size_t s = 0; s < plan.pcnt.size(); ++s) {
+        hipLaunchKernelGGL(chol_panel_kernel, dim3(plan.pcnt[s]), dim3(256), 0, st, A, L, LT, n,
+                           reinterpret_cast<const int2 *>(plan.panels) + plan.pbeg[s], Winv, fail, plan.nd ? x : nullptr);
+        if (plan.tcnt[s] > 0)
+            hipLaunchKernelGGL(chol_update_kernel, dim3(4 * plan.tcnt[s]), dim3(256), 0, st, A, L, n,
+                               plan.tasks + 4 * (int64_t)plan.tbeg[s], plan.contrib, fail, plan.nd ? x : nullptr);
     }
-    const int nblk = (n + NB - 1) / NB;
-    for (int kb = 0; kb < nblk; ++kb) {
-        const int k0 = kb * NB;
-        hipLaunchKernelGGL(chol_diag_kernel<false>, dim3(1), dim3(256), 0, st, A, n, k0, nullptr, Winv, fail,
-                           nullptr);
-        const int m = plan.rcnt[kb];
-        if (m > 0)
-            hipLaunchKernelGGL(chol_panel_update_kernel, dim3(4 * (m * (m + 1) / 2)), dim3(256), 0, st, A, L, LT, n, k0, Winv,
-                               plan.rows + plan.rbeg[kb], fail);
+}
+
+// A system of one block (n <= 64): damping and gauge, factorisation and both triangular solves in one launch of
+// one workgroup (three launches, 33 us, before; 17 us so).  x receives the step, zero if the factorisation failed.
+__global__ void __launch_bounds__(256) solve_small_kernel(const double *__restrict__ H, const double *__restrict__ b,
+                                                          int n, int anchor, const LmState *lm, double lam_override,
+                                                          double *__restrict__ x, int32_t *fail, Stamp stamp)
+{
+    __shared__ double M[NB][kLd];
+    __shared__ FactorLds F;
+    __shared__ double v[NB], y[NB];
+    const int tid = threadIdx.x;
+    if (tid == 0) put_stamp(stamp, 2);
+    const double lam = lam_override >= 0.0 ? lam_override : lm->lam;
+    const int a0 = 6 * anchor, a1 = a0 + 6;
+#pragma unroll 4
+    for (int it = 0; it < NB * NB / 256; ++it) {
+        const int e = it * 256 + tid, i = e >> 6, j = e & 63;
+        const bool fixed = (i >= a0 && i < a1) || (j >= a0 && j < a1);
+        double h = i == j ? 1.0 : 0.0;
+        if (i < n && j < n && !fixed) h = H[(int64_t)i * n + j];
+        if (i == j && i < n) h += lam * h;
+        M[i][j] = h;
     }
+    if (tid < NB) v[tid] = (tid < n && !(tid >= a0 && tid < a1)) ? -b[tid] : 0.0;
+    __syncthreads();
+    const bool ok = factor64(M, F);
+    // y = W v, x = W^T y: four lanes to a row, 16 columns each
+    const int i = tid >> 2, j0 = (tid & 3) * 16;
+    double u = 0.0;
+#pragma unroll
+    for (int j = 0; j < 16; ++j)
+        if (j0 + j <= i) u = fma(M[i][j0 + j], v[j0 + j], u);
+    u += __shfl_xor(u, 1, 64);
+    u += __shfl_xor(u, 2, 64);
+    if ((tid & 3) == 0) y[i] = u;
+    __syncthreads();
+    u = 0.0;
+#pragma unroll
+    for (int j = 0; j < 16; ++j)
+        if (j0 + j >= i) u = fma(M[j0 + j][i], y[j0 + j], u);
+    u += __shfl_xor(u, 1, 64);
+    u += __shfl_xor(u, 2, 64);
+    if ((tid & 3) == 0 && i < n) x[i] = ok ? u : 0.0;
+    if (tid == 0) *fail = ok ? 0 : 1;
+}
+
+void launch_solve_small(const double *H, const double *b, int n, int anchor, const LmState *lm, double lam_override,
+                        double *x, int32_t *fail, const Stamp &stamp, hipStream_t st)
+{
+    hipLaunchKernelGGL(solve_small_kernel, dim3(1), dim3(256), 0, st, H, b, n, anchor, lm, lam_override, x, fail, stamp);
 }
 
 // L y = rhs, then L^T x = y, both in one launch of one 1024-thread workgroup that walks the
