@@ -106,8 +106,10 @@ struct EvalArgs {
     int32_t num_cu;              // compute units of the device
     void *partials;              // double[n_items][kAcc]
     double omega_g, omega_d, omega_n, huber;
-    // loss adjoint outputs (adjoint launches only): arenas laid out like the images
-    float *g_int, *g_dep, *g_nrm;
+    // loss adjoint outputs (adjoint launches only): one plane per channel (I, depth, nx, ny, nz), g_plane floats
+    // apart, each laid out like the images
+    float *g;
+    int64_t g_plane;
     double adj_scale;
     // z-buffer occlusion variant (nullptr: off): per pair, Ht * Wt FP32 depth bits at zbuf + zoff[pair]
     uint32_t *zbuf;
@@ -192,6 +194,13 @@ void launch_zbuffer_pass(const EvalArgs &a, int src_model, int tgt_model, int it
 void launch_eval_adjoint(const EvalArgs &a, int channels, int src_model, int tgt_model, int item_base, int n_items,
                          int grid, hipStream_t st);
 void launch_pose_grad(const double *b, const float *delta, double scale, float *grad, int N, hipStream_t st);
+// Where one keyframe's image gradients go (each nullptr: not wanted), its texel offset in the planes and its size.
+struct GradOut {
+    float *gi, *gd, *gn;
+    int64_t off;
+    int32_t npx, pad;
+};
+void launch_grad_out(const float *g, int64_t plane, const GradOut *outs, int n, int max_px, hipStream_t st);
 void launch_delta_to_dx(const float *delta, double *dx, int N, hipStream_t st);
 void launch_reduce_pairs(const void *partials, int precision, const int32_t *pair_items,
                          const int32_t *pair_item_begin, const int32_t *pair_item_count, const PairDev *pairs,

@@ -89,7 +89,7 @@ struct pba_ctx {
     int64_t zcells = 0;
     DevBuf H, b, H_cand, b_cand, totals, A, Winv, dx, lm, fail, logbuf;
     DevBuf dbg_status, dbg_uv, dbg_cell, dbg_res;
-    DevBuf loss_delta, loss_poses, g_int, g_dep, g_nrm, g_pose;
+    DevBuf loss_delta, loss_poses, g_img, g_out, g_stage, g_pose;
     bool loss_ready = false;
 
     // one captured LM iteration (replayed by pba_iterate)
@@ -880,7 +880,7 @@ pba_status pba_destroy(pba_ctx *c)
                       &c->counters, &c->partials, &c->pair_out, &c->blk_rc, &c->blk_ptr, &c->blk_ent, &c->bk_ptr,
                       &c->bk_ent, &c->H, &c->b, &c->H_cand, &c->b_cand, &c->totals, &c->A, &c->Winv, &c->dx, &c->lm,
                       &c->fail, &c->logbuf, &c->dbg_status, &c->dbg_uv, &c->dbg_cell, &c->dbg_res,
-                      &c->loss_delta, &c->loss_poses, &c->g_int, &c->g_dep, &c->g_nrm, &c->g_pose,
+                      &c->loss_delta, &c->loss_poses, &c->g_img, &c->g_out, &c->g_stage, &c->g_pose,
                       &c->chol_rows, &c->chol_cols, &c->chol_meta, &c->zbuf, &c->zoff, &c->nd_perm,
                       &c->nd_off, &c->nd_dtiles, &c->nd_lcols, &c->nd_panels, &c->nd_tasks, &c->nd_contrib, &c->dx_nat};
     drop_graph(c);
@@ -1353,29 +1353,18 @@ pba_status pba_loss_backward(pba_ctx *c, double grad_F, float *grad_delta, float
     const int N = c->NP;   // pose variables
     const int64_t tx = c->L().texels;
     const bool five = c->cfg.channels == 5;
-    if ((s = ensure(c, c->g_int, (size_t)tx * 4))) return s;
-    if ((s = ensure(c, c->g_dep, (size_t)tx * 4))) return s;
-    if (five && (s = ensure(c, c->g_nrm, (size_t)tx * 12))) return s;
+    const int nch = five ? 5 : 2;
+    const int64_t plane = (tx + 31) / 32 * 32;
+    if ((s = ensure(c, c->g_img, (size_t)(nch * plane) * 4))) return s;
     if ((s = ensure(c, c->g_pose, (size_t)N * 24))) return s;
-    // zero the gradient arenas with a fill kernel (as doubles over the byte range)
-    launch_fill(P_<double>(c->g_int), (int64_t)tx / 2, 0.0, c->stream);
-    launch_fill(P_<double>(c->g_dep), (int64_t)tx / 2, 0.0, c->stream);
-    if (tx & 1) {
-        HIP_OK(hipMemsetAsync(P_<float>(c->g_int) + tx - 1, 0, 4, c->stream));
-        HIP_OK(hipMemsetAsync(P_<float>(c->g_dep) + tx - 1, 0, 4, c->stream));
-    }
-    if (five) {
-        launch_fill(P_<double>(c->g_nrm), (int64_t)tx * 3 / 2, 0.0, c->stream);
-        if ((tx * 3) & 1) HIP_OK(hipMemsetAsync(P_<float>(c->g_nrm) + 3 * tx - 1, 0, 4, c->stream));
-    }
+    launch_fill(P_<double>(c->g_img), nch * plane / 2, 0.0, c->stream);   // (as doubles)
     // recompute the evaluation at X0 boxplus delta in adjoint mode
     const int ngrp = (int)c->groups.size();
     setup_pairs(c, P_<double>(c->loss_poses), PoseStep{}, P_<uint32_t>(c->counters), ngrp * kXcd, Stamp{}, c->stream);
     zbuffer_pass(c, P_<double>(c->loss_poses), c->stream, ctx_work(c));
     EvalArgs a = make_args(c);
-    a.g_int = P_<float>(c->g_int);
-    a.g_dep = P_<float>(c->g_dep);
-    a.g_nrm = five ? P_<float>(c->g_nrm) : nullptr;
+    a.g = P_<float>(c->g_img);
+    a.g_plane = plane;
     a.adj_scale = grad_F;
     for (int g = 0; g < ngrp; ++g) {
         const auto &G = c->groups[g];
@@ -1388,19 +1377,51 @@ pba_status pba_loss_backward(pba_ctx *c, double grad_F, float *grad_delta, float
     launch_assemble(P_<double>(c->pair_out), c->P, P_<int2>(c->blk_rc), P_<int32_t>(c->blk_ptr),
                     P_<int32_t>(c->blk_ent), c->nblk, P_<int32_t>(c->bk_ptr), P_<int32_t>(c->bk_ent), N,
                     P_<double>(c->H_cand), P_<double>(c->b_cand), P_<double>(c->totals) + 4, nullptr, c->stream);
-    launch_pose_grad(P_<double>(c->b_cand), P_<float>(c->loss_delta), grad_F, P_<float>(c->g_pose), N, c->stream);
+    launch_pose_grad(P_<double>(c->b_cand), P_<float>(c->loss_delta), grad_F,
+                     on_device && grad_delta ? grad_delta : P_<float>(c->g_pose), N, c->stream);
     HIP_OK(hipGetLastError());
-    const hipMemcpyKind kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-    if (grad_delta) HIP_OK(hipMemcpyAsync(grad_delta, c->g_pose.p, (size_t)N * 24, kind, c->stream));
-    for (int k = 0; k < c->N; ++k) {   // every keyframe (pose variables may be shared)
-        const size_t npx = (size_t)c->L().kfs_h[k].H * c->L().kfs_h[k].W;
-        const int64_t off = c->L().kfs_h[k].off;
+    if (!on_device && grad_delta)
+        HIP_OK(hipMemcpyAsync(grad_delta, c->g_pose.p, (size_t)N * 24, hipMemcpyDeviceToHost, c->stream));
+    // every keyframe's image gradients (pose variables may be shared): device outputs in one launch; for host
+    // outputs the launch only interleaves the normals, and each array is copied
+    const std::vector<KfDev> &kfs = c->L().kfs_h;
+    std::vector<GradOut> outs;
+    int max_px = 0;
+    if (!on_device && five && grad_normals && (s = ensure(c, c->g_stage, (size_t)tx * 12))) return s;
+    for (int k = 0; k < c->N; ++k) {
+        GradOut o{};
+        o.off = kfs[k].off;
+        o.npx = kfs[k].H * kfs[k].W;
+        if (on_device) {
+            o.gi = grad_intensity ? grad_intensity[k] : nullptr;
+            o.gd = grad_depth ? grad_depth[k] : nullptr;
+            o.gn = five && grad_normals ? grad_normals[k] : nullptr;
+        } else if (five && grad_normals && grad_normals[k]) {
+            o.gn = P_<float>(c->g_stage) + 3 * o.off;
+        }
+        if (!o.gi && !o.gd && !o.gn) continue;
+        max_px = std::max(max_px, o.npx);
+        outs.push_back(o);
+    }
+    if (!outs.empty()) {
+        if ((s = upload(c, c->g_out, outs.data(), outs.size() * sizeof(GradOut)))) return s;
+        for (size_t k = 0; k < outs.size(); k += 32768) {   // (a grid's y extent is at most 65535)
+            const int n = (int)std::min<size_t>(32768, outs.size() - k);
+            launch_grad_out(P_<float>(c->g_img), plane, P_<GradOut>(c->g_out) + k, n, max_px, c->stream);
+        }
+        HIP_OK(hipGetLastError());
+    }
+    for (int k = 0; k < c->N && !on_device; ++k) {
+        const size_t npx = (size_t)kfs[k].H * kfs[k].W;
+        const int64_t off = kfs[k].off;
+        const float *g = P_<float>(c->g_img) + off;
         if (grad_intensity && grad_intensity[k])
-            HIP_OK(hipMemcpyAsync(grad_intensity[k], P_<float>(c->g_int) + off, npx * 4, kind, c->stream));
+            HIP_OK(hipMemcpyAsync(grad_intensity[k], g, npx * 4, hipMemcpyDeviceToHost, c->stream));
         if (grad_depth && grad_depth[k])
-            HIP_OK(hipMemcpyAsync(grad_depth[k], P_<float>(c->g_dep) + off, npx * 4, kind, c->stream));
+            HIP_OK(hipMemcpyAsync(grad_depth[k], g + plane, npx * 4, hipMemcpyDeviceToHost, c->stream));
         if (five && grad_normals && grad_normals[k])
-            HIP_OK(hipMemcpyAsync(grad_normals[k], P_<float>(c->g_nrm) + 3 * off, npx * 12, kind, c->stream));
+            HIP_OK(hipMemcpyAsync(grad_normals[k], P_<float>(c->g_stage) + 3 * off, npx * 12, hipMemcpyDeviceToHost,
+                                  c->stream));
     }
     HIP_OK(hipStreamSynchronize(c->stream));
     return PBA_OK;
