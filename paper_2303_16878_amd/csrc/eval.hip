@@ -1213,59 +1213,73 @@ __global__ void __launch_bounds__(kBlock)
     }
 }
 
-// Depth-interval plane of one keyframe (one thread per texel (kc, kr)): over the cells (x0, y0) in
+// Depth-interval planes of the spherical keyframes (keyframe kf0 + blockIdx.z; one thread per texel (kc, kr), row
+// kr = blockIdx.y; a launch per keyframe cost more than its 4 us of work): over the cells (x0, y0) in
 // {kc - 1, kc} x {kr - 1, kr} with the stencil inside the image, those whose 12 depth taps span at most
 // 2 tau + 1e-6 m (a wider span fails the gate max(dmax - zeta, zeta - dmin) <= tau for every zeta, FP64
 // rounding included) give lo = min of their largest taps and hi = max of their smallest taps.  A point
 // passing the gate in one of them has dmax - zeta <= tau and zeta - dmin <= tau there, hence, rounding
 // being monotone, lo - zeta <= tau and zeta - hi <= tau.
-__global__ void gate_plane_kernel(const float *__restrict__ dep, float2 *__restrict__ out, int H, int W, double tau)
+__global__ void __launch_bounds__(128) gate_plane_kernel(const float *__restrict__ dep_all, float2 *__restrict__ out_all,
+                                                         const KfDev *__restrict__ kfs,
+                                                         const SensorDev *__restrict__ sensors, int kf0)
 {
-    const int kc = blockIdx.x * blockDim.x + threadIdx.x, kr = blockIdx.y;
-    if (kc >= W) return;
-    // the 5 x 5 texels rows kr - 2 .. kr + 2, columns kc - 2 .. kc + 2 hold every tap of the four cells
-    float d[5][5];
+    const KfDev kf = kfs[kf0 + blockIdx.z];
+    const SensorDev &sen = sensors[kf.sensor];
+    const int H = kf.H, W = kf.W;
+    const int kc = blockIdx.x * blockDim.x + threadIdx.x;
+    if (sen.model != MODEL_SPHERICAL || kc >= W) return;
+    const double tau = sen.taud;
+    const float *dep = dep_all + kf.off;
+    float2 *out = out_all + kf.off;
+    for (int kr = blockIdx.y; kr < H; kr += gridDim.y) {
+        // the 5 x 5 texels rows kr - 2 .. kr + 2, columns kc - 2 .. kc + 2 hold every tap of the four cells
+        float d[5][5];
 #pragma unroll
-    for (int i = 0; i < 5; ++i)
+        for (int i = 0; i < 5; ++i)
 #pragma unroll
-        for (int j = 0; j < 5; ++j) {
-            const int y = kr - 2 + i, x = kc - 2 + j;
-            d[i][j] = (y >= 0 && y < H && x >= 0 && x < W) ? dep[(int64_t)y * W + x] : kNoDepth;
+            for (int j = 0; j < 5; ++j) {
+                const int y = kr - 2 + i, x = kc - 2 + j;
+                d[i][j] = (y >= 0 && y < H && x >= 0 && x < W) ? dep[(int64_t)y * W + x] : kNoDepth;
+            }
+        float lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+        for (int dy = -1; dy <= 0; ++dy)
+#pragma unroll
+            for (int dx = -1; dx <= 0; ++dx) {
+                const int x0 = kc + dx, y0 = kr + dy;
+                if (x0 < 1 || x0 > W - 3 || y0 < 1 || y0 > H - 3) continue;
+                // in d, row y0 of cell (x0, y0) is index dy + 2 and its column x0 index dx + 2
+                const int r = dy + 2, c = dx + 2;
+                const float t[12] = {d[r][c - 1], d[r][c], d[r][c + 1], d[r][c + 2], d[r + 1][c - 1], d[r + 1][c],
+                                     d[r + 1][c + 1], d[r + 1][c + 2], d[r - 1][c], d[r - 1][c + 1], d[r + 2][c],
+                                     d[r + 2][c + 1]};
+                float mn = t[0], mx = t[0];
+#pragma unroll
+                for (int k = 1; k < 12; ++k) { mn = fminf(mn, t[k]); mx = fmaxf(mx, t[k]); }
+                if ((double)mx - (double)mn > 2.0 * tau + 1e-6) continue;
+                lo = fminf(lo, mx);
+                hi = fmaxf(hi, mn);
+            }
+        // Predicted depths zeta that can pass: zeta >= lo - tau and zeta <= hi + tau (up to FP64 rounding).  The
+        // evaluation tests an FP32 zf within 2e-7 relative of zeta, so the bounds are widened by 1e-6 relative
+        // and 1e-9 m and rounded outwards to FP32.
+        float2 r = make_float2(INFINITY, -INFINITY);
+        if (lo < INFINITY) {
+            const double l = (double)lo - tau, h = (double)hi + tau;
+            r.x = __double2float_rd(l - 1e-6 * fabs(l) - 1e-9);
+            r.y = __double2float_ru(h + 1e-6 * fabs(h) + 1e-9);
         }
-    float lo = INFINITY, hi = -INFINITY;
-#pragma unroll
-    for (int dy = -1; dy <= 0; ++dy)
-#pragma unroll
-        for (int dx = -1; dx <= 0; ++dx) {
-            const int x0 = kc + dx, y0 = kr + dy;
-            if (x0 < 1 || x0 > W - 3 || y0 < 1 || y0 > H - 3) continue;
-            // in d, row y0 of cell (x0, y0) is index dy + 2 and its column x0 index dx + 2
-            const int r = dy + 2, c = dx + 2;
-            const float t[12] = {d[r][c - 1], d[r][c], d[r][c + 1], d[r][c + 2], d[r + 1][c - 1], d[r + 1][c],
-                                 d[r + 1][c + 1], d[r + 1][c + 2], d[r - 1][c], d[r - 1][c + 1], d[r + 2][c],
-                                 d[r + 2][c + 1]};
-            float mn = t[0], mx = t[0];
-#pragma unroll
-            for (int k = 1; k < 12; ++k) { mn = fminf(mn, t[k]); mx = fmaxf(mx, t[k]); }
-            if ((double)mx - (double)mn > 2.0 * tau + 1e-6) continue;
-            lo = fminf(lo, mx);
-            hi = fmaxf(hi, mn);
-        }
-    // Predicted depths zeta that can pass: zeta >= lo - tau and zeta <= hi + tau (up to FP64 rounding).  The
-    // evaluation tests an FP32 zf within 2e-7 relative of zeta, so the bounds are widened by 1e-6 relative
-    // and 1e-9 m and rounded outwards to FP32.
-    float2 r = make_float2(INFINITY, -INFINITY);
-    if (lo < INFINITY) {
-        const double l = (double)lo - tau, h = (double)hi + tau;
-        r.x = __double2float_rd(l - 1e-6 * fabs(l) - 1e-9);
-        r.y = __double2float_ru(h + 1e-6 * fabs(h) + 1e-9);
+        out[(int64_t)kr * W + kc] = r;
     }
-    out[(int64_t)kr * W + kc] = r;
 }
 
-void launch_gate_plane(const float *dep, float2 *gate, int H, int W, double tau, hipStream_t st)
+void launch_gate_planes(const float *dep, float2 *gate, const KfDev *kfs, const SensorDev *sensors, int n, int max_h,
+                        int max_w, hipStream_t st)
 {
-    hipLaunchKernelGGL(gate_plane_kernel, dim3((W + 127) / 128, H), dim3(128), 0, st, dep, gate, H, W, tau);
+    for (int k = 0; k < n; k += 32768)   // (a grid's y and z extents are at most 65535)
+        hipLaunchKernelGGL(gate_plane_kernel, dim3((max_w + 127) / 128, std::min(max_h, 32768), std::min(n - k, 32768)),
+                           dim3(128), 0, st, dep, gate, kfs, sensors, k);
 }
 
 // One persistent launch of an evaluation kernel: at most `grid` workgroups and no more than give each

@@ -288,21 +288,24 @@ NdArrays nd_arrays(const TilePattern &tp, const std::vector<int> &pos);
 // only the backward sweeps); x is ignored in the natural order.
 void launch_cholesky(double *A, double *L, double *LT, int n, double *Winv, const CholPlan &plan, int32_t *fail,
                      hipStream_t st, double *x);
-// Depth-interval plane of one keyframe (H x W depth plane `dep`, occlusion bound tau): texel (kc, kr)
-// holds, over the cells (x0, y0) in {kc - 1, kc} x {kr - 1, kr} whose stencil lies inside the image and
+// Depth-interval planes of the spherical ones among n keyframes (depth planes in `dep`, tau their sensor's occlusion
+// bound; max_h, max_w over them): texel (kc, kr) holds, over the cells (x0, y0) in {kc - 1, kc} x {kr - 1, kr} whose stencil lies inside the image and
 // whose 12 depth taps span at most 2 tau (+1e-6 m), with lo = the smallest of their largest taps and
 // hi = the largest of their smallest taps, the predicted-depth range [lo - tau, hi + tau] widened by
 // 1e-6 relative and 1e-9 m and rounded outwards to FP32 (+inf / -inf where there is no such cell).
-void launch_gate_plane(const float *dep, float2 *gate, int H, int W, double tau, hipStream_t st);
+void launch_gate_planes(const float *dep, float2 *gate, const KfDev *kfs, const SensorDev *sensors, int n, int max_h,
+                        int max_w, hipStream_t st);
 // att / att2: the attribute plane of one keyframe (att_get4 / att_get1 layout, `five` cues or one,
 // `bf` BF16 storage)
 void launch_downsample(const float *dep, const void *att, int five, int bf, int H, int W, float *dep2, void *att2,
                        int H2, int W2, double tau, hipStream_t st);
 void launch_unpack(const float *dep, const void *att, int five, int bf, int npx, float *I, float *D, float *N,
                    hipStream_t st);
-void launch_normals(const float *dep, void *att4, int bf, int H, int W, const double2 *lcol, const double2 *lrow,
-                    int spherical, double scale, double min_px, double max_px, double tau, int min_count,
+// Normals of the n keyframes of one sensor model (max_px <= 16; max_tiles: the most normals_tiles among them).
+void launch_normals(const float *dep, void *att4, int bf, const KfDev *kfs, const SensorDev *sensors, const double2 *lut,
+                    int n, int max_tiles, bool spherical, double radius_m, double min_px, double max_px, int min_count,
                     hipStream_t st);
+int normals_tiles(int H, int W);
 // Solves L L^T x = x in place with the factor as launch_cholesky leaves it (nested dissection: x
 // holds y from launch_cholesky, and only L^T x = y remains).
 void launch_chol_solve(const double *L, const double *LT, double *Winv, double *x, int n, const CholPlan &plan,

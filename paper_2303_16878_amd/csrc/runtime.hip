@@ -89,7 +89,7 @@ struct pba_ctx {
     int64_t zcells = 0;
     DevBuf H, b, H_cand, b_cand, totals, A, Winv, dx, lm, fail, logbuf;
     DevBuf dbg_status, dbg_uv, dbg_cell, dbg_res;
-    DevBuf loss_delta, loss_poses, g_img, g_out, g_stage, g_pose;
+    DevBuf kf_in, loss_delta, loss_poses, g_img, g_out, g_stage, g_pose;
     bool loss_ready = false;
 
     // one captured LM iteration (replayed by pba_iterate)
@@ -189,21 +189,28 @@ int n_sys(const pba_ctx *c) { return 6 * c->NP; }
 int pose_var(const pba_ctx *c, int kf) { return c->pose_of.empty() ? kf : c->pose_of[kf]; }
 
 // texel preparation: sanitise depth (invalid -> 0; the depth test is made in FP64, as the
-// sensor's limits are given) and split into the depth plane and the attribute plane
-__global__ void pack_kernel(const float *__restrict__ I, const float *__restrict__ D, const float *__restrict__ Nn,
-                            float *__restrict__ dep, void *__restrict__ att, int five, int bf, int npx, double dmin,
-                            double dmax)
+// sensor's limits are given) and split into the depth plane and the attribute plane.  Keyframe in0 + blockIdx.y of
+// the table; one launch for all of them (a launch per keyframe took 8 us of the host each, for 3 us of work).
+struct KfIn {
+    const float *I, *D, *N;
+    int64_t off;
+    double dmin, dmax;
+    int32_t npx, pad;
+};
+__global__ void __launch_bounds__(256) pack_kernel(const KfIn *__restrict__ in, int in0, float *__restrict__ dep_all,
+                                                   void *__restrict__ att, int five, int bf)
 {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < npx; i += gridDim.x * blockDim.x) {
-        const float d = D[i];
-        const bool ok = isfinite(d) && d > 0.f && (double)d >= dmin && (double)d <= dmax;
-        const float in = I[i];
-        dep[i] = ok ? d : kNoDepth;
+    const KfIn f = in[in0 + blockIdx.y];
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < f.npx; i += gridDim.x * blockDim.x) {
+        const float d = f.D[i];
+        const bool ok = isfinite(d) && d > 0.f && (double)d >= f.dmin && (double)d <= f.dmax;
+        const float v = f.I[i];
+        dep_all[f.off + i] = ok ? d : kNoDepth;
         if (five) {
-            const float n0 = Nn[3 * (int64_t)i], n1 = Nn[3 * (int64_t)i + 1], n2 = Nn[3 * (int64_t)i + 2];
-            att_put4(att, bf, i, ok ? make_float4(in, n0, n1, n2) : make_float4(0.f, 0.f, 0.f, 0.f));
+            const float n0 = f.N[3 * (int64_t)i], n1 = f.N[3 * (int64_t)i + 1], n2 = f.N[3 * (int64_t)i + 2];
+            att_put4(att, bf, f.off + i, ok ? make_float4(v, n0, n1, n2) : make_float4(0.f, 0.f, 0.f, 0.f));
         } else {
-            att_put1(att, bf, i, ok ? in : 0.f);
+            att_put1(att, bf, f.off + i, ok ? v : 0.f);
         }
     }
 }
@@ -308,10 +315,15 @@ pba_status image_layout(pba_ctx *c, ImageSet &is, const std::vector<int32_t> &se
 // its depth plane (enqueued on the context stream; rebuilt whenever the depth plane is written).
 void build_gate(pba_ctx *c, ImageSet &is)
 {
+    int h = 0, w = 0;
     for (const KfDev &f : is.kfs_h)
-        if (is.sensors_dev_h[f.sensor].model == MODEL_SPHERICAL)
-            launch_gate_plane(P_<float>(is.dep) + f.off, P_<float2>(is.gate) + f.off, f.H, f.W,
-                              is.sensors_dev_h[f.sensor].taud, c->stream);
+        if (is.sensors_dev_h[f.sensor].model == MODEL_SPHERICAL) {
+            h = std::max(h, f.H);
+            w = std::max(w, f.W);
+        }
+    if (h > 0)
+        launch_gate_planes(P_<float>(is.dep), P_<float2>(is.gate), P_<KfDev>(is.kfs_d), P_<SensorDev>(is.sensors_d),
+                           (int)is.kfs_h.size(), h, w, c->stream);
 }
 
 // Tiles (64 x 64) of the Cholesky factor of the 6 NP x 6 NP system that can be nonzero: those
@@ -880,7 +892,7 @@ pba_status pba_destroy(pba_ctx *c)
                       &c->counters, &c->partials, &c->pair_out, &c->blk_rc, &c->blk_ptr, &c->blk_ent, &c->bk_ptr,
                       &c->bk_ent, &c->H, &c->b, &c->H_cand, &c->b_cand, &c->totals, &c->A, &c->Winv, &c->dx, &c->lm,
                       &c->fail, &c->logbuf, &c->dbg_status, &c->dbg_uv, &c->dbg_cell, &c->dbg_res,
-                      &c->loss_delta, &c->loss_poses, &c->g_img, &c->g_out, &c->g_stage, &c->g_pose,
+                      &c->kf_in, &c->loss_delta, &c->loss_poses, &c->g_img, &c->g_out, &c->g_stage, &c->g_pose,
                       &c->chol_rows, &c->chol_cols, &c->chol_meta, &c->zbuf, &c->zoff, &c->nd_perm,
                       &c->nd_off, &c->nd_dtiles, &c->nd_lcols, &c->nd_panels, &c->nd_tasks, &c->nd_contrib, &c->dx_nat};
     drop_graph(c);
@@ -933,7 +945,7 @@ pba_status pba_load_keyframes(pba_ctx *c, int32_t n, const int32_t *sensor_id, c
             return fail(c, PBA_EINVAL, "keyframe %d: null image", k);
         sensor_of[k] = sid;
     }
-    pba_status s;
+    pba_status s = PBA_OK;
     const int prev_level = c->level;
     const bool same_layout = c->N == n && (int)c->lv[0].kfs_h.size() == n &&
                              std::equal(sensor_of.begin(), sensor_of.end(), c->lv[0].kfs_h.begin(),
@@ -944,34 +956,54 @@ pba_status pba_load_keyframes(pba_ctx *c, int32_t n, const int32_t *sensor_id, c
     c->level = 0;
     ImageSet &is = c->lv[0];
     is.sensors = c->sensors;
-    if ((s = sensor_tables(c, is))) return s;
-    if (!same_layout) c->pose_of.clear();   // a new keyframe set starts with one pose per keyframe
-    if ((s = image_layout(c, is, sensor_of))) return s;
-    const std::vector<KfDev> &kfs = is.kfs_h;
-    // stage each keyframe on the device (copy if host) and pack
-    DevBuf stage;
-    for (int k = 0; k < n; ++k) {
-        const int npx = kfs[k].H * kfs[k].W;
-        const pba_sensor &S = c->sensors[kfs[k].sensor];
-        const float *dI = intensity[k], *dD = depth[k], *dN = c->cfg.channels == 5 ? normals[k] : nullptr;
-        if (!on_device) {
-            const size_t need = (size_t)npx * (c->cfg.channels == 5 ? 5 : 2) * 4;
-            if ((s = ensure(c, stage, need))) { release(stage); return s; }
-            float *base = P_<float>(stage);
-            HIP_OK(hipMemcpyAsync(base, intensity[k], (size_t)npx * 4, hipMemcpyHostToDevice, c->stream));
-            HIP_OK(hipMemcpyAsync(base + npx, depth[k], (size_t)npx * 4, hipMemcpyHostToDevice, c->stream));
-            if (dN) HIP_OK(hipMemcpyAsync(base + 2 * (size_t)npx, normals[k], (size_t)npx * 12, hipMemcpyHostToDevice,
-                                          c->stream));
-            dI = base; dD = base + npx; dN = dN ? base + 2 * (size_t)npx : nullptr;
-        }
-        const int blocks = std::min((npx + 255) / 256, 4096);
-        const bool five = c->cfg.channels == 5;
-        hipLaunchKernelGGL(pack_kernel, dim3(blocks), dim3(256), 0, c->stream, dI, dD, five ? dN : nullptr,
-                           P_<float>(c->L().dep) + kfs[k].off,
-                           static_cast<char *>(att_plane(c, c->L())) + kfs[k].off * att_bytes(c), five ? 1 : 0,
-                           c->cfg.storage_bf16, npx, S.min_depth, S.max_depth);
-        if (!on_device) HIP_OK(hipStreamSynchronize(c->stream));   // stage is reused
+    if (!same_layout) {   // (the tables and the layout of an equal set are in place)
+        if ((s = sensor_tables(c, is))) return s;
+        c->pose_of.clear();   // a new keyframe set starts with one pose per keyframe
+        if ((s = image_layout(c, is, sensor_of))) return s;
     }
+    const std::vector<KfDev> &kfs = is.kfs_h;
+    // pack: device images in place, host images staged one keyframe after the other
+    const bool five = c->cfg.channels == 5;
+    std::vector<KfIn> in(n);
+    for (int k = 0; k < n; ++k) {
+        const pba_sensor &S = c->sensors[kfs[k].sensor];
+        in[k] = KfIn{intensity[k], depth[k], five ? normals[k] : nullptr, kfs[k].off, S.min_depth, S.max_depth,
+                     kfs[k].H * kfs[k].W, 0};
+    }
+    DevBuf stage;
+    size_t need = 0;
+    for (int k = 0; k < n && !on_device; ++k) need = std::max(need, (size_t)in[k].npx * (five ? 5 : 2) * 4);
+    if (!on_device && (s = ensure(c, stage, need))) return s;
+    auto staged = [&](int k) -> pba_status {
+        KfIn &f = in[k];
+        float *base = P_<float>(stage);
+        const size_t npx = (size_t)f.npx;
+        HIP_OK(hipMemcpyAsync(base, f.I, npx * 4, hipMemcpyHostToDevice, c->stream));
+        HIP_OK(hipMemcpyAsync(base + npx, f.D, npx * 4, hipMemcpyHostToDevice, c->stream));
+        if (f.N) HIP_OK(hipMemcpyAsync(base + 2 * npx, f.N, npx * 12, hipMemcpyHostToDevice, c->stream));
+        f.I = base; f.D = base + npx; f.N = f.N ? base + 2 * npx : nullptr;
+        return PBA_OK;
+    };
+    auto pack = [&](int k0, int cnt) -> pba_status {
+        pba_status e = upload(c, c->kf_in, in.data() + k0, (size_t)cnt * sizeof(KfIn));
+        if (e) return e;
+        int most = 0;
+        for (int k = k0; k < k0 + cnt; ++k) most = std::max(most, in[k].npx);
+        for (int b = 0; b < cnt; b += 32768)   // (a grid's y extent is at most 65535)
+            hipLaunchKernelGGL(pack_kernel, dim3(std::min((most + 255) / 256, 4096), std::min(cnt - b, 32768)), dim3(256), 0,
+                               c->stream, P_<KfIn>(c->kf_in), b, P_<float>(is.dep), att_plane(c, is), five ? 1 : 0,
+                               c->cfg.storage_bf16);
+        return PBA_OK;
+    };
+    if (on_device) {
+        s = pack(0, n);
+    } else {
+        for (int k = 0; k < n && !s; ++k) {
+            if ((s = staged(k)) || (s = pack(k, 1))) break;
+            if (hipStreamSynchronize(c->stream) != hipSuccess) s = fail(c, PBA_EDEVICE, "loading keyframe %d", k);   // stage is reused
+        }
+    }
+    if (s) { release(stage); return s; }
     build_gate(c, is);
     HIP_OK(hipGetLastError());
     HIP_OK(hipStreamSynchronize(c->stream));
@@ -1445,17 +1477,16 @@ pba_status pba_estimate_normals(pba_ctx *c, double radius_m, double min_px, doub
         }
     }
     ImageSet &is = c->lv[0];
-    for (int k = 0; k < c->N; ++k) {
-        const KfDev &f = is.kfs_h[k];
-        const pba_sensor &S = is.sensors[f.sensor];
-        const SensorDev &sd = is.sensors_dev_h[f.sensor];
-        const double tau = S.model == PBA_PINHOLE ? c->cfg.occlusion_tau_pinhole : c->cfg.occlusion_tau_spherical;
-        launch_normals(P_<float>(is.dep) + f.off, static_cast<char *>(is.att4.p) + f.off * att_bytes(c),
-                       c->cfg.storage_bf16, f.H, f.W,
-                       P_<double2>(is.lut64) + sd.lut_col, P_<double2>(is.lut64) + sd.lut_row,
-                       S.model == PBA_SPHERICAL, radius_m * std::fabs(S.fx), min_px, max_px, tau, min_count,
-                       c->stream);
+    int tiles[2] = {0, 0};   // the most tiles of a keyframe, per sensor model
+    for (const KfDev &f : is.kfs_h) {
+        int &m = tiles[is.sensors_dev_h[f.sensor].model == MODEL_SPHERICAL];
+        m = std::max(m, normals_tiles(f.H, f.W));
     }
+    for (int sph = 0; sph < 2; ++sph)
+        if (tiles[sph] > 0)
+            launch_normals(P_<float>(is.dep), is.att4.p, c->cfg.storage_bf16, P_<KfDev>(is.kfs_d),
+                           P_<SensorDev>(is.sensors_d), P_<double2>(is.lut64), c->N, tiles[sph], sph != 0, radius_m, min_px,
+                           max_px, min_count, c->stream);
     HIP_OK(hipGetLastError());
     HIP_OK(hipStreamSynchronize(c->stream));
     drop_graph(c);
@@ -1690,6 +1721,11 @@ pba_status pba_get_level_image(pba_ctx *c, int32_t level, int32_t kf, float *int
     launch_unpack(P_<float>(is.dep) + f.off, static_cast<char *>(att_plane(c, is)) + f.off * att_bytes(c), five ? 1 : 0,
                   c->cfg.storage_bf16, (int)npx, I, D, five ? N : nullptr, c->stream);
     hipError_t e = hipGetLastError();
+    if (e == hipSuccess && five && intensity && depth == intensity + npx && normals == depth + npx) {
+        // outputs laid out like the staging buffer: one copy
+        e = hipMemcpyAsync(intensity, I, npx * 20, hipMemcpyDeviceToHost, c->stream);
+        intensity = depth = normals = nullptr;
+    }
     if (e == hipSuccess && intensity) e = hipMemcpyAsync(intensity, I, npx * 4, hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess && depth) e = hipMemcpyAsync(depth, D, npx * 4, hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess && normals) {

@@ -71,3 +71,35 @@ def test_normals_match_oracle(fixture, request, pba):
         # the estimated normals feed the evaluation: one evaluation runs and counts pixels
         ev = ctx.evaluate()
         assert ev["n_valid"] > 0
+
+
+@pytest.mark.parametrize("radius_m,min_px,max_px", [(0.1, 2.0, 5.0), (0.5, 0.0, 16.0), (0.02, 1.5, 2.5), (0.05, 3.0, 3.0)])
+@pytest.mark.parametrize("name", ["rgbd", "lidar", "joint"])
+def test_tile_edges_and_radii(pba, name, radius_m, min_px, max_px):
+    """Images that end inside a 32 x 8 tile, windows from one pixel to the largest, both models in one context:
+    has-normal masks and angles against the oracle's fits, where the fit is well conditioned (middle eigenvalue
+    above 1e-6 of the trace, the smallest below a tenth of it), to 1e-6 rad."""
+    if name == "rgbd":
+        prob = synth.make("rgbd_small", H=37, W=67, n_kf=2)
+    elif name == "lidar":
+        prob = synth.make("lidar128", H=21, W=129, n_kf=300, kfs=[0, 1]).subset([0, 1])
+    else:
+        prob = synth.make("joint", H_l=17, W_l=97, H_c=25, W_c=33, kfs=[0, 200]).subset([0, 200])
+    with pba.context_for_problem(prob, channels=5) as ctx:
+        ctx.estimate_normals(radius_m=radius_m, min_px=min_px, max_px=max_px, min_count=3)
+        for k in range(prob.n):
+            sen = prob.sensors[prob.kf_sensor[k]]
+            tau = prob.params["occ_tau_pinhole"] if sen["model"] == 0 else prob.params["occ_tau_spherical"]
+            want, ok, w, cnt = oracle.estimate_normals(sen, prob.depth[k], radius_m, min_px, max_px, tau, 3)
+            got = ctx.get_level_image(0, k)[2].astype(np.float64)
+            tr = np.maximum(w.sum(-1), 1e-300)
+            clear = (w[..., 1] > 1e-6 * tr) & (cnt >= 3)
+            assert np.array_equal((np.abs(got).sum(-1) > 0)[clear], ok[clear])
+            assert not np.any(got[cnt < 3])
+            fit = clear & ok & (w[..., 0] < 0.1 * w[..., 1])
+            ang = np.linalg.norm(np.cross(got[fit], want[fit].astype(np.float64)), axis=-1)
+            assert ang.max(initial=0.0) <= 1e-6, (k, ang.max(initial=0.0))
+            # orientation n . q < 0, undecided where the plane holds the sensor (three neighbours in one image row)
+            q = oracle.unproject_image(sen, prob.depth[k])
+            decided = fit & (np.abs(np.sum(want * q, -1)) > 1e-6 * np.linalg.norm(q, axis=-1))
+            assert np.all(np.sum(got[decided] * want[decided], -1) > 0)
