@@ -456,9 +456,11 @@ class Context:
         dims = np.zeros(2, np.int32)
         self._check(self.lib.pba_get_level_image(self.h, int(level), int(kf), None, None, None, dims.ctypes.data))
         H, W = int(dims[0]), int(dims[1])
-        I = np.empty((H, W), np.float32)
-        D = np.empty((H, W), np.float32)
-        N = np.empty((H, W, 3), np.float32)
+        # one block for the three images: one copy from the device, and an allocation of several MB is backed by
+        # large pages where the system has them (fresh 4 KB pages cost more than the copy into them)
+        block = np.empty(5 * H * W, np.float32)
+        I, D = block[:H * W].reshape(H, W), block[H * W:2 * H * W].reshape(H, W)
+        N = block[2 * H * W:].reshape(H, W, 3)
         self._check(self.lib.pba_get_level_image(self.h, int(level), int(kf), I.ctypes.data, D.ctypes.data,
                                                  N.ctypes.data, None))
         return I, D, N

@@ -313,6 +313,7 @@ void launch_chol_solve(const double *L, const double *LT, double *Winv, double *
 // off: first element of each pose variable's 6 in dx (nested-dissection layout), nullptr = 6 k.
 void launch_boxplus(const double *X, const double *dx, const int32_t *off, double *Xout, int N, hipStream_t st);
 void launch_gather_step(double *dst, const double *src, const int32_t *off, int N, hipStream_t st);
+void launch_lm_init(LmState *lm, const double *totals, double lam, int use_lm, hipStream_t st);
 void launch_lm_decide(LmState *lm, const double *totals_cand, const int2 *blk_rc, int nblk, double *H_cur,
                       const double *H_cand, double *b_cur, const double *b_cand, double *X_cur, const double *X_cand,
                       int N, double *totals_cur, double *logbuf, int log_cap, hipStream_t st);

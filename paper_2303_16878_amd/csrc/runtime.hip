@@ -475,8 +475,10 @@ int default_items_px(pba_ctx *c, const std::vector<int32_t> &src, const std::vec
     return need <= (int64_t)kScratchBytes ? (int)size : 4096;
 }
 
-pba_status build_plan(pba_ctx *c, const std::vector<int32_t> &src, const std::vector<int32_t> &tgt)
+// The work queue of the active level (a captured iteration holds its buffers and counts, so it is dropped).
+pba_status build_items(pba_ctx *c, const std::vector<int32_t> &src, const std::vector<int32_t> &tgt)
 {
+    drop_graph(c);
     const int P = (int)src.size();
     c->items_px = c->tuned_px ? c->tuned_px : default_items_px(c, src, tgt);
     // work items: (pair, first source pixel); grouped by (source model, target model),
@@ -537,7 +539,28 @@ pba_status build_plan(pba_ctx *c, const std::vector<int32_t> &src, const std::ve
     if ((s = ensure(c, c->partials, (size_t)std::max(1, c->n_items) * kAcc * sizeof(double)))) return s;
     if ((s = ensure(c, c->pair_out, (size_t)std::max(1, P) * kPairOut * 8))) return s;
     if ((s = ensure(c, c->pair_dev, (size_t)std::max(1, P) * sizeof(PairDev)))) return s;
+    if ((s = ensure(c, c->counters, 64 * 4 * kCtrStride))) return s;
+    if (c->cfg.occlusion_zbuffer) {   // one z-buffer per pair, sized for its target at this level
+        std::vector<int64_t> zo(std::max(P, 1), 0);
+        int64_t tot = 0;
+        for (int p = 0; p < P; ++p) {
+            zo[p] = tot;
+            tot += (int64_t)c->L().kfs_h[tgt[p]].H * c->L().kfs_h[tgt[p]].W;
+        }
+        if ((s = upload(c, c->zoff, zo.data(), zo.size() * 8))) return s;
+        if ((s = ensure(c, c->zbuf, (size_t)(tot + 2) * 4))) return s;   // whole doubles for the fill
+        c->zcells = tot;
+    }
+    return PBA_OK;
+}
 
+// Everything that follows from the pairs: the work queue, and what does not depend on the level (a level switch
+// rebuilds the queue alone), the assembly's lists and the factorisation's plan.
+pba_status build_plan(pba_ctx *c, const std::vector<int32_t> &src, const std::vector<int32_t> &tgt)
+{
+    const int P = (int)src.size();
+    pba_status s;
+    if ((s = build_items(c, src, tgt))) return s;
     // assembly plan: contributions of each nonzero 6x6 block, in pair order
     std::map<std::pair<int, int>, std::vector<int32_t>> blocks;
     // keyed by pose variable: a pair inside one rig frame adds all four blocks to its diagonal
@@ -571,18 +594,6 @@ pba_status build_plan(pba_ctx *c, const std::vector<int32_t> &src, const std::ve
     if ((s = upload(c, c->blk_ent, ent.data(), ent.size() * 4))) return s;
     if ((s = upload(c, c->bk_ptr, bptr.data(), bptr.size() * 4))) return s;
     if ((s = upload(c, c->bk_ent, bent.data(), bent.size() * 4))) return s;
-    if ((s = ensure(c, c->counters, 64 * 4 * kCtrStride))) return s;
-    if (c->cfg.occlusion_zbuffer) {   // one z-buffer per pair, sized for its target at this level
-        std::vector<int64_t> zo(std::max(P, 1), 0);
-        int64_t tot = 0;
-        for (int p = 0; p < P; ++p) {
-            zo[p] = tot;
-            tot += (int64_t)c->L().kfs_h[tgt[p]].H * c->L().kfs_h[tgt[p]].W;
-        }
-        if ((s = upload(c, c->zoff, zo.data(), zo.size() * 8))) return s;
-        if ((s = ensure(c, c->zbuf, (size_t)(tot + 2) * 4))) return s;   // whole doubles for the fill
-        c->zcells = tot;
-    }
     return build_chol_plan(c, src, tgt);
 }
 
@@ -665,10 +676,9 @@ void zbuffer_pass(pba_ctx *c, const double *poses, hipStream_t st, const WorkBuf
 // with the context's HIP events; `step` (launches of an iteration) evaluates at the poses moved by the
 // step, which the setup stores in step->Xo, stamps the evaluation into the LM log row (the events would only
 // keep a captured graph's last replay) and decides whether the step is accepted.
-pba_status run_eval(pba_ctx *c, const double *poses, double *H, double *b, double *totals, bool timed,
-                    hipStream_t st, const PoseStep *step = nullptr, const WorkBufs *work = nullptr)
+// eval_pairs stops at the per-pair records.
+pba_status eval_pairs(pba_ctx *c, const double *poses, bool timed, hipStream_t st, const PoseStep *step, const WorkBufs &w)
 {
-    const WorkBufs w = work ? *work : ctx_work(c);
     const int ngrp = (int)c->groups.size();
     const Stamp stamp = step ? Stamp{step->lm, P_<double>(c->logbuf), c->log_cap} : Stamp{};
     setup_pairs(c, poses, step ? *step : PoseStep{}, w.counters, ngrp * kXcd, stamp, st);
@@ -686,6 +696,16 @@ pba_status run_eval(pba_ctx *c, const double *poses, double *H, double *b, doubl
     HIP_OK(hipGetLastError());
     launch_reduce_pairs(w.partials, c->cfg.precision, P_<int32_t>(c->pitems), P_<int32_t>(c->ibeg),
                         P_<int32_t>(c->icnt), P_<PairDev>(c->pair_dev), w.pair_out, c->P, stamp, st);
+    HIP_OK(hipGetLastError());
+    return PBA_OK;
+}
+
+pba_status run_eval(pba_ctx *c, const double *poses, double *H, double *b, double *totals, bool timed,
+                    hipStream_t st, const PoseStep *step = nullptr, const WorkBufs *work = nullptr)
+{
+    const WorkBufs w = work ? *work : ctx_work(c);
+    pba_status s = eval_pairs(c, poses, timed, st, step, w);
+    if (s) return s;
     launch_assemble(w.pair_out, c->P, P_<int2>(c->blk_rc), P_<int32_t>(c->blk_ptr),
                     P_<int32_t>(c->blk_ent), c->nblk, P_<int32_t>(c->bk_ptr), P_<int32_t>(c->bk_ent), c->NP, H, b,
                     totals, step ? step->lm : nullptr, st);
@@ -1012,7 +1032,7 @@ pba_status pba_load_keyframes(pba_ctx *c, int32_t n, const int32_t *sensor_id, c
     c->system_valid = false;
     c->loss_ready = false;
     if (same_layout) {   // images replaced; poses and pairs kept (the plan follows level 0 again)
-        if (prev_level != 0 && c->P > 0 && (s = build_plan(c, c->src_h, c->tgt_h))) return s;
+        if (prev_level != 0 && c->P > 0 && (s = build_items(c, c->src_h, c->tgt_h))) return s;
         return PBA_OK;
     }
     c->N = n;
@@ -1275,15 +1295,9 @@ pba_status pba_iterate(pba_ctx *c, int32_t n_iters, int32_t use_lm, double lambd
             return s;
         c->system_valid = true;
     }
-    double tot0[4];
-    HIP_OK(hipMemcpyAsync(tot0, totals, sizeof tot0, hipMemcpyDeviceToHost, c->stream));
-    HIP_OK(hipStreamSynchronize(c->stream));
-    LmState lm{};
-    lm.lam = use_lm ? (lambda0 > 0.0 ? lambda0 : (c->lam_carry > 0.0 ? c->lam_carry : 1e-4)) : 0.0;
-    lm.F_cur = tot0[0];
-    lm.valid_cur = (int64_t)tot0[2];
-    lm.use_lm = use_lm ? 1 : 0;
-    HIP_OK(hipMemcpyAsync(c->lm.p, &lm, sizeof lm, hipMemcpyHostToDevice, c->stream));
+    launch_lm_init(P_<LmState>(c->lm), totals,
+                   use_lm ? (lambda0 > 0.0 ? lambda0 : (c->lam_carry > 0.0 ? c->lam_carry : 1e-4)) : 0.0, use_lm ? 1 : 0,
+                   c->stream);
     HIP_OK(hipEventRecord(c->ev0, c->stream));
     if (c->cfg.use_graph) {
         if (!c->graph_valid) {
@@ -1473,7 +1487,7 @@ pba_status pba_estimate_normals(pba_ctx *c, double radius_m, double min_px, doub
         c->lv.resize(1);
         if (c->level != 0) {
             c->level = 0;
-            if (c->P > 0 && (s = build_plan(c, c->src_h, c->tgt_h))) return s;
+            if (c->P > 0 && (s = build_items(c, c->src_h, c->tgt_h))) return s;
         }
     }
     ImageSet &is = c->lv[0];
@@ -1534,11 +1548,21 @@ pba_status pba_build_pairs(pba_ctx *c, double max_angle, double max_dist, double
     pba_status st;
     std::vector<int32_t> ks, kt;
     if (!cs.empty()) {
-        if ((st = pba_set_pairs(c, (int32_t)cs.size(), cs.data(), ct.data()))) return st;
-        if ((st = run_eval(c, P_<double>(c->poses), P_<double>(c->H_cand), P_<double>(c->b_cand),
-                           P_<double>(c->totals) + 4, false, c->stream)))
-            return st;
-        std::vector<double> po((size_t)c->P * kPairOut);
+        // the candidates' records only: no assembly lists, no factorisation plan, no system for them (the context
+        // has no pairs until the kept ones are set)
+        std::vector<int2> pr(cs.size());
+        for (size_t k = 0; k < cs.size(); ++k) pr[k] = make_int2(cs[k], ct[k]);
+        c->P = 0;
+        c->system_valid = false;
+        c->lam_carry = -1.0;
+        c->chol.rows = nullptr;
+        if ((st = upload(c, c->pairs_d, pr.data(), pr.size() * sizeof(int2)))) return st;
+        if ((st = build_items(c, cs, ct))) return st;
+        c->P = (int)cs.size();
+        st = eval_pairs(c, P_<double>(c->poses), false, c->stream, nullptr, ctx_work(c));
+        c->P = 0;
+        if (st) return st;
+        std::vector<double> po(cs.size() * kPairOut);
         HIP_OK(hipMemcpyAsync(po.data(), c->pair_out.p, po.size() * 8, hipMemcpyDeviceToHost, c->stream));
         HIP_OK(hipStreamSynchronize(c->stream));
         for (size_t k = 0; k < cs.size(); ++k) {
@@ -1573,7 +1597,7 @@ pba_status pba_autotune(pba_ctx *c, pba_tune_point *points, int32_t max_points, 
     double best = 1e300;
     for (int si = 0; si < 6; ++si) {
         c->tuned_px = sizes[si];
-        if ((s = build_plan(c, c->src_h, c->tgt_h))) return s;
+        if ((s = build_items(c, c->src_h, c->tgt_h))) return s;
         for (int gi = 0; gi < 3; ++gi) {
             c->grid = c->num_cu * mult[gi];
             double ms = 0.0;
@@ -1592,7 +1616,7 @@ pba_status pba_autotune(pba_ctx *c, pba_tune_point *points, int32_t max_points, 
     }
     c->tuned_px = best_px;
     c->grid = best_grid;
-    if ((s = build_plan(c, c->src_h, c->tgt_h))) return s;
+    if ((s = build_items(c, c->src_h, c->tgt_h))) return s;
     drop_graph(c);
     HIP_OK(hipStreamSynchronize(c->stream));
     if (n_points) *n_points = std::min(n, max_points);
@@ -1658,7 +1682,7 @@ pba_status pba_set_level(pba_ctx *c, int32_t level)
     c->loss_ready = false;
     c->lam_carry = -1.0;
     pba_status s;
-    if (c->P > 0 && (s = build_plan(c, c->src_h, c->tgt_h))) return s;
+    if (c->P > 0 && (s = build_items(c, c->src_h, c->tgt_h))) return s;
     HIP_OK(hipStreamSynchronize(c->stream));
     return PBA_OK;
 }

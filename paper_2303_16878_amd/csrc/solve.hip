@@ -857,6 +857,23 @@ void launch_lm_decide(LmState *lm, const double *totals_cand, const int2 *blk_rc
                        totals_cur, blk_rc, nblk, H_cur, H_cand, b_cur, b_cand, X_cur, X_cand, N, logbuf, log_cap);
 }
 
+// The state ahead of the first iteration: F and the valid count from the current system's totals (read here, so
+// that the host waits for nothing before it enqueues the iterations).
+__global__ void lm_init_kernel(LmState *lm, const double *__restrict__ totals, double lam, int use_lm)
+{
+    LmState s{};
+    s.lam = lam;
+    s.F_cur = totals[0];
+    s.valid_cur = (int64_t)totals[2];
+    s.use_lm = use_lm;
+    *lm = s;
+}
+
+void launch_lm_init(LmState *lm, const double *totals, double lam, int use_lm, hipStream_t st)
+{
+    hipLaunchKernelGGL(lm_init_kernel, dim3(1), dim3(1), 0, st, lm, totals, lam, use_lm);
+}
+
 __global__ void copy_kernel(double *__restrict__ dst, const double *__restrict__ src, int64_t n)
 {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
