@@ -50,6 +50,7 @@ struct ImageSet {
     int64_t texels = 0;
     DevBuf sensors_d, kfs_d, dep, att4, att1, lut32, lut64;
     DevBuf gate;   // depth-interval plane (launch_gate_plane), one float2 per texel
+    bool laid_out = false;   // tables, layout and planes are complete (not after an allocation that failed)
 };
 
 struct pba_ctx {
@@ -976,10 +977,12 @@ pba_status pba_load_keyframes(pba_ctx *c, int32_t n, const int32_t *sensor_id, c
     c->level = 0;
     ImageSet &is = c->lv[0];
     is.sensors = c->sensors;
-    if (!same_layout) {   // (the tables and the layout of an equal set are in place)
+    if (!same_layout || !is.laid_out) {   // (the tables and the layout of an equal set are in place)
+        is.laid_out = false;
         if ((s = sensor_tables(c, is))) return s;
-        c->pose_of.clear();   // a new keyframe set starts with one pose per keyframe
+        if (!same_layout) c->pose_of.clear();   // a new keyframe set starts with one pose per keyframe
         if ((s = image_layout(c, is, sensor_of))) return s;
+        is.laid_out = true;
     }
     const std::vector<KfDev> &kfs = is.kfs_h;
     // pack: device images in place, host images staged one keyframe after the other
