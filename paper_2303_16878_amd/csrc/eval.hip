@@ -1282,7 +1282,7 @@ void launch_gate_planes(const float *dep, float2 *gate, const KfDev *kfs, const 
                            dim3(128), 0, st, dep, gate, kfs, sensors, k);
 }
 
-// One persistent launch of an evaluation kernel: at most `grid` workgroups and no more than give each
+// One persistent launch of an evaluation kernel: at most `grid` workgroups (0: as many as fit) and no more than give each
 // wave one item (per queue), so that few items spread one wave to a SIMD.  n_static: the workgroups the chip
 // holds at once (the kernel's occupancy); a workgroup beyond them may start only when others have left,
 // so it gets no item by position.
@@ -1292,6 +1292,7 @@ static void launch_items(K kernel, int per_cu, const EvalArgs &a, int item_base,
     if (n_items <= 0) return;
     constexpr int kWaves = kBlock / 64;
     const int per_queue = (n_items + kXcd - 1) / kXcd;
+    if (grid == 0) grid = std::max(per_cu, 4) * a.num_cu;   // all that the chip holds
     grid = std::max(1, std::min(grid, (per_queue + kWaves - 1) / kWaves * kXcd));
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), 0, st, a, item_base, n_items, std::min(grid, per_cu * a.num_cu));
 }

@@ -107,6 +107,7 @@ struct pba_ctx {
     double wall_khz = 0.0;   // device wall-clock rate
     int64_t eval_launches = 0, iterations = 0;
     int grid = 0;
+    bool full_grid = false;   // launches take every workgroup the chip holds of their kernel, at least `grid`
 };
 
 namespace {
@@ -454,6 +455,10 @@ EvalArgs make_args(pba_ctx *c);
 // balance: 7000 pairs of 64x1024 take 3.66 ms in items of 4096, 4.41 in items of 2048.  Below, waves without
 // an item idle: 20 pairs of 120x160 take 85 / 17 / 13 us in items of 4096 / 512 / 128, 56 pairs of 240x320
 // 135 / 75 us in items of 4096 / 1024.
+// Two cues between pinhole sensors (FP32) fit six waves to a SIMD where the grid holds four.  They are launched in
+// full where every wave gets 1024 pixels or more (full_grid): 1000 pairs of 480x640 take 7.0 ms for three
+// evaluations and two steps, 7.5 on the grid; 180 of 240x320 1.48, 1.55 for five steps.  With less, the ends of the
+// smaller items cost more than the waves give: ten steps of 20 pairs of 120x160 take 646 us so, 598 on the grid.
 int default_items_px(pba_ctx *c, const std::vector<int32_t> &src, const std::vector<int32_t> &tgt)
 {
     int64_t px[4] = {0, 0, 0, 0};
@@ -464,7 +469,9 @@ int default_items_px(pba_ctx *c, const std::vector<int32_t> &src, const std::vec
     const int k = (int)(std::max_element(px, px + 4) - px);
     const int per_cu = launch_eval(make_args(c), c->cfg.precision, c->cfg.channels, c->cfg.grad_mode, k >> 1, k & 1, false,
                                    0, 0, 0, c->stream);
-    const int64_t waves = std::max<int64_t>(1, std::min<int64_t>((int64_t)per_cu * c->num_cu, c->grid)) * (kBlock / 64);
+    const int64_t full = std::max<int64_t>(1, (int64_t)per_cu * c->num_cu) * (kBlock / 64);
+    c->full_grid = px[k] >= 1024 * full;
+    const int64_t waves = c->full_grid ? full : std::min<int64_t>(full, (int64_t)c->grid * (kBlock / 64));
     const int64_t size = std::min<int64_t>(4096, std::max<int64_t>(64, ((px[k] + waves - 1) / waves + 63) / 64 * 64));
     // (a queue that the allocation-free evaluation's array holds in items of 4096 stays one)
     int64_t items = 0;
@@ -481,6 +488,7 @@ pba_status build_items(pba_ctx *c, const std::vector<int32_t> &src, const std::v
 {
     drop_graph(c);
     const int P = (int)src.size();
+    c->full_grid = false;
     c->items_px = c->tuned_px ? c->tuned_px : default_items_px(c, src, tgt);
     // work items: (pair, first source pixel); grouped by (source model, target model),
     // ordered by target keyframe so items sharing a target image run close together
@@ -690,8 +698,8 @@ pba_status eval_pairs(pba_ctx *c, const double *poses, bool timed, hipStream_t s
     for (int g = 0; g < ngrp; ++g) {
         const auto &G = c->groups[g];
         a.counter = w.counters + g * kXcd * kCtrStride;
-        launch_eval(a, c->cfg.precision, c->cfg.channels, c->cfg.grad_mode, G.sm, G.tm, false, G.base, G.count, c->grid,
-                    st);
+        launch_eval(a, c->cfg.precision, c->cfg.channels, c->cfg.grad_mode, G.sm, G.tm, false, G.base, G.count,
+                    c->full_grid ? 0 : c->grid, st);
     }
     if (timed) HIP_OK(hipEventRecord(c->ev1, st));
     HIP_OK(hipGetLastError());
