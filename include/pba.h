@@ -34,7 +34,10 @@
  * whether a caller pointer is device memory (1) or host memory (0).
  *
  * Errors: every call returns a pba_status; no C++ exception crosses the ABI.
- * On error the context state is unchanged and pba_last_error() describes it.
+ * On error the context state is unchanged and pba_last_error() describes it; but a
+ * pba_load_keyframes that runs out of device memory (PBA_ENOMEM) or meets a device
+ * error leaves no keyframes loaded (PBA_ESTATE from what needs them until a load
+ * succeeds).
  *
  * Streams: work is ordered on the stream given in pba_config (a borrowed
  * hipStream_t; NULL = the null stream).  Calls that return host values

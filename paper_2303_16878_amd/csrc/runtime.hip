@@ -50,7 +50,6 @@ struct ImageSet {
     int64_t texels = 0;
     DevBuf sensors_d, kfs_d, dep, att4, att1, lut32, lut64;
     DevBuf gate;   // depth-interval plane (launch_gate_plane), one float2 per texel
-    bool laid_out = false;   // tables, layout and planes are complete (not after an allocation that failed)
 };
 
 struct pba_ctx {
@@ -820,6 +819,98 @@ pba_status ensure_system(pba_ctx *c)
     return PBA_OK;
 }
 
+// The keyframes and all that follows from them given up: the context is as before its first load (the sensors stay).
+void drop_keyframes(pba_ctx *c)
+{
+    drop_graph(c);
+    for (size_t l = 1; l < c->lv.size(); ++l) release_images(c->lv[l]);
+    c->lv.resize(1);
+    c->level = 0;
+    c->N = c->NP = c->P = 0;
+    c->pose_of.clear();
+    c->chol.rows = nullptr;
+    c->poses_set = c->system_valid = c->loss_ready = false;
+}
+
+// pba_load_keyframes after its checks.  Poses and pairs are kept where every keyframe's sensor is as before; else the
+// old set is dropped first, so that a failure on the way leaves none of it to be taken for the new one.
+pba_status load_images(pba_ctx *c, const std::vector<int32_t> &sensor_of, const float *const *intensity,
+                       const float *const *depth, const float *const *normals, int32_t on_device)
+{
+    pba_status s = PBA_OK;
+    const int n = (int)sensor_of.size(), prev_level = c->level;
+    const bool same_layout = c->N == n && std::equal(sensor_of.begin(), sensor_of.end(), c->lv[0].kfs_h.begin(),
+                                                     [](int32_t a, const KfDev &f) { return a == f.sensor; });
+    if (!same_layout) drop_keyframes(c);
+    // a new load drops any pyramid: level 0 becomes the only and active level
+    for (size_t l = 1; l < c->lv.size(); ++l) release_images(c->lv[l]);
+    c->lv.resize(1);
+    c->level = 0;
+    c->system_valid = false;
+    c->loss_ready = false;
+    drop_graph(c);
+    ImageSet &is = c->lv[0];
+    if (!same_layout) {   // (the tables, the layout and the poses of an equal set are in place)
+        is.sensors = c->sensors;
+        if ((s = sensor_tables(c, is))) return s;
+        if ((s = image_layout(c, is, sensor_of))) return s;
+        if ((s = ensure(c, c->poses, (size_t)n * 12 * 8))) return s;
+        if ((s = ensure(c, c->poses_cand, (size_t)n * 12 * 8))) return s;
+    }
+    const std::vector<KfDev> &kfs = is.kfs_h;
+    // pack: device images in place, host images staged one keyframe after the other
+    const bool five = c->cfg.channels == 5;
+    std::vector<KfIn> in(n);
+    for (int k = 0; k < n; ++k) {
+        const pba_sensor &S = c->sensors[kfs[k].sensor];
+        in[k] = KfIn{intensity[k], depth[k], five ? normals[k] : nullptr, kfs[k].off, S.min_depth, S.max_depth,
+                     kfs[k].H * kfs[k].W, 0};
+    }
+    DevBuf stage;
+    size_t need = 0;
+    for (int k = 0; k < n && !on_device; ++k) need = std::max(need, (size_t)in[k].npx * (five ? 5 : 2) * 4);
+    if (!on_device && (s = ensure(c, stage, need))) return s;
+    auto staged = [&](int k) -> pba_status {
+        KfIn &f = in[k];
+        float *base = P_<float>(stage);
+        const size_t npx = (size_t)f.npx;
+        HIP_OK(hipMemcpyAsync(base, f.I, npx * 4, hipMemcpyHostToDevice, c->stream));
+        HIP_OK(hipMemcpyAsync(base + npx, f.D, npx * 4, hipMemcpyHostToDevice, c->stream));
+        if (f.N) HIP_OK(hipMemcpyAsync(base + 2 * npx, f.N, npx * 12, hipMemcpyHostToDevice, c->stream));
+        f.I = base; f.D = base + npx; f.N = f.N ? base + 2 * npx : nullptr;
+        return PBA_OK;
+    };
+    auto pack = [&](int k0, int cnt) -> pba_status {
+        pba_status e = upload(c, c->kf_in, in.data() + k0, (size_t)cnt * sizeof(KfIn));
+        if (e) return e;
+        int most = 0;
+        for (int k = k0; k < k0 + cnt; ++k) most = std::max(most, in[k].npx);
+        for (int b = 0; b < cnt; b += 32768)   // (a grid's y extent is at most 65535)
+            hipLaunchKernelGGL(pack_kernel, dim3(std::min((most + 255) / 256, 4096), std::min(cnt - b, 32768)), dim3(256), 0,
+                               c->stream, P_<KfIn>(c->kf_in), b, P_<float>(is.dep), att_plane(c, is), five ? 1 : 0,
+                               c->cfg.storage_bf16);
+        return PBA_OK;
+    };
+    if (on_device) {
+        s = pack(0, n);
+    } else {
+        for (int k = 0; k < n && !s; ++k) {
+            if ((s = staged(k)) || (s = pack(k, 1))) break;
+            if (hipStreamSynchronize(c->stream) != hipSuccess) s = fail(c, PBA_EDEVICE, "loading keyframe %d", k);   // stage is reused
+        }
+    }
+    if (!s) build_gate(c, is);
+    if (!s && (hipGetLastError() != hipSuccess || hipStreamSynchronize(c->stream) != hipSuccess))
+        s = fail(c, PBA_EDEVICE, "loading %d keyframes", n);
+    release(stage);
+    if (s) return s;
+    // (of an equal set the images alone are replaced; the plan follows level 0 again)
+    if (same_layout) return prev_level != 0 && c->P > 0 ? build_items(c, c->src_h, c->tgt_h) : PBA_OK;
+    c->N = n;
+    c->NP = n;
+    return PBA_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -974,87 +1065,10 @@ pba_status pba_load_keyframes(pba_ctx *c, int32_t n, const int32_t *sensor_id, c
             return fail(c, PBA_EINVAL, "keyframe %d: null image", k);
         sensor_of[k] = sid;
     }
-    pba_status s = PBA_OK;
-    const int prev_level = c->level;
-    const bool same_layout = c->N == n && (int)c->lv[0].kfs_h.size() == n &&
-                             std::equal(sensor_of.begin(), sensor_of.end(), c->lv[0].kfs_h.begin(),
-                                        [](int32_t a, const KfDev &f) { return a == f.sensor; });
-    // a new load drops any pyramid: level 0 becomes the only and active level
-    for (size_t l = 1; l < c->lv.size(); ++l) release_images(c->lv[l]);
-    c->lv.resize(1);
-    c->level = 0;
-    ImageSet &is = c->lv[0];
-    is.sensors = c->sensors;
-    if (!same_layout || !is.laid_out) {   // (the tables and the layout of an equal set are in place)
-        is.laid_out = false;
-        if ((s = sensor_tables(c, is))) return s;
-        if (!same_layout) c->pose_of.clear();   // a new keyframe set starts with one pose per keyframe
-        if ((s = image_layout(c, is, sensor_of))) return s;
-        is.laid_out = true;
-    }
-    const std::vector<KfDev> &kfs = is.kfs_h;
-    // pack: device images in place, host images staged one keyframe after the other
-    const bool five = c->cfg.channels == 5;
-    std::vector<KfIn> in(n);
-    for (int k = 0; k < n; ++k) {
-        const pba_sensor &S = c->sensors[kfs[k].sensor];
-        in[k] = KfIn{intensity[k], depth[k], five ? normals[k] : nullptr, kfs[k].off, S.min_depth, S.max_depth,
-                     kfs[k].H * kfs[k].W, 0};
-    }
-    DevBuf stage;
-    size_t need = 0;
-    for (int k = 0; k < n && !on_device; ++k) need = std::max(need, (size_t)in[k].npx * (five ? 5 : 2) * 4);
-    if (!on_device && (s = ensure(c, stage, need))) return s;
-    auto staged = [&](int k) -> pba_status {
-        KfIn &f = in[k];
-        float *base = P_<float>(stage);
-        const size_t npx = (size_t)f.npx;
-        HIP_OK(hipMemcpyAsync(base, f.I, npx * 4, hipMemcpyHostToDevice, c->stream));
-        HIP_OK(hipMemcpyAsync(base + npx, f.D, npx * 4, hipMemcpyHostToDevice, c->stream));
-        if (f.N) HIP_OK(hipMemcpyAsync(base + 2 * npx, f.N, npx * 12, hipMemcpyHostToDevice, c->stream));
-        f.I = base; f.D = base + npx; f.N = f.N ? base + 2 * npx : nullptr;
-        return PBA_OK;
-    };
-    auto pack = [&](int k0, int cnt) -> pba_status {
-        pba_status e = upload(c, c->kf_in, in.data() + k0, (size_t)cnt * sizeof(KfIn));
-        if (e) return e;
-        int most = 0;
-        for (int k = k0; k < k0 + cnt; ++k) most = std::max(most, in[k].npx);
-        for (int b = 0; b < cnt; b += 32768)   // (a grid's y extent is at most 65535)
-            hipLaunchKernelGGL(pack_kernel, dim3(std::min((most + 255) / 256, 4096), std::min(cnt - b, 32768)), dim3(256), 0,
-                               c->stream, P_<KfIn>(c->kf_in), b, P_<float>(is.dep), att_plane(c, is), five ? 1 : 0,
-                               c->cfg.storage_bf16);
-        return PBA_OK;
-    };
-    if (on_device) {
-        s = pack(0, n);
-    } else {
-        for (int k = 0; k < n && !s; ++k) {
-            if ((s = staged(k)) || (s = pack(k, 1))) break;
-            if (hipStreamSynchronize(c->stream) != hipSuccess) s = fail(c, PBA_EDEVICE, "loading keyframe %d", k);   // stage is reused
-        }
-    }
-    if (s) { release(stage); return s; }
-    build_gate(c, is);
-    HIP_OK(hipGetLastError());
-    HIP_OK(hipStreamSynchronize(c->stream));
-    release(stage);
-    drop_graph(c);
-    c->system_valid = false;
-    c->loss_ready = false;
-    if (same_layout) {   // images replaced; poses and pairs kept (the plan follows level 0 again)
-        if (prev_level != 0 && c->P > 0 && (s = build_items(c, c->src_h, c->tgt_h))) return s;
-        return PBA_OK;
-    }
-    c->N = n;
-    c->NP = n;
-    c->P = 0;
-    c->chol.rows = nullptr;
-    c->poses_set = false;
-    if ((s = ensure(c, c->poses, (size_t)n * 12 * 8))) return s;
-    if ((s = ensure(c, c->poses_cand, (size_t)n * 12 * 8))) return s;
     if (c->cfg.anchor >= n) return fail(c, PBA_EINVAL, "anchor %d >= number of keyframes %d", c->cfg.anchor, n);
-    return PBA_OK;
+    const pba_status s = load_images(c, sensor_of, intensity, depth, normals, on_device);
+    if (s) drop_keyframes(c);   // the old set is gone in part: nothing may work on the rest
+    return s;
 }
 
 pba_status pba_set_poses(pba_ctx *c, int32_t n, const double *poses, int32_t on_device)

@@ -1,0 +1,173 @@
+"""Calls that run out of device memory: for every allocation of the call in turn, the call reports PBA_ENOMEM, nothing
+works on what it left half done (PBA_ESTATE until the missing part is given again), and once it is given the
+results are those of a new context."""
+import contextlib
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+SMALL, LARGE = 0, 1
+SIZES = ((24, 32), (48, 72))
+
+
+@pytest.fixture(scope="module")
+def pba():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    import paper_2303_16878_amd as pba
+    pba.load_library()
+    return pba
+
+
+@contextlib.contextmanager
+def memory_for(n_alloc):
+    """Device memory for n_alloc more allocations (None: no limit)."""
+    import torch
+    real, calls = torch.cuda.caching_allocator_alloc, []
+
+    def limited(*args, **kw):
+        calls.append(args)
+        if n_alloc is not None and len(calls) > n_alloc:
+            raise torch.cuda.OutOfMemoryError("limit of the test")
+        return real(*args, **kw)
+
+    torch.cuda.caching_allocator_alloc = limited
+    try:
+        yield calls
+    finally:
+        torch.cuda.caching_allocator_alloc = real
+
+
+def _images(which, n, seed=0):
+    H, W = SIZES[which]
+    rng = np.random.default_rng(1000 * seed + H * W)
+    depth = [np.full((H, W), 2.0, np.float32) + 0.01 * rng.random((H, W), dtype=np.float32) for _ in range(n)]
+    return [rng.random((H, W), dtype=np.float32) for _ in range(n)], depth
+
+
+def _poses(n):
+    X = np.tile(np.hstack([np.eye(3).ravel(), np.zeros(3)]), (n, 1))
+    X[:, 9] = 0.01 * np.arange(n)
+    return X
+
+
+PAIRS = [(0, 1), (1, 0)]
+
+
+def _context(pba, **kw):
+    ctx = pba.Context(channels=2, **kw)
+    for H, W in SIZES:
+        ctx.add_sensor(0, H, W, 0.8 * W, 0.8 * W, (W - 1) / 2, (H - 1) / 2, 0.1, 10.0)
+    return ctx
+
+
+def _loaded(pba, which, n, groups=None, **kw):
+    ctx = _context(pba, **kw)
+    ctx.load_keyframes([which] * n, *_images(which, n), None)
+    if groups is not None:
+        ctx.set_pose_groups(groups)
+    ctx.set_poses(_poses(ctx.n_poses))
+    ctx.set_pairs(PAIRS)
+    return ctx
+
+
+def _equal(a, b):
+    assert a["n_valid"] > 0 and a["F"] == b["F"] and a["n_valid"] == b["n_valid"]
+    assert np.array_equal(a["H"], b["H"]) and np.array_equal(a["b"], b["b"])
+
+
+def _refused(pba, call, status=None):
+    with pytest.raises(pba.PbaError) as e:
+        call()
+    assert e.value.status == (pba.PBA_ESTATE if status is None else status), e.value
+    return True
+
+
+def _out_of_memory(pba, call, k):
+    """True if the call fails for want of memory with k allocations left to it, False if it gets by."""
+    with memory_for(k) as calls:
+        try:
+            call()
+            return False
+        except pba.PbaError as e:
+            assert e.status == pba.PBA_ENOMEM and len(calls) == k + 1, e
+            print("out of memory at allocation %d" % k, flush=True)
+            return True
+
+
+@pytest.mark.parametrize("zbuffer", [False, True])
+@pytest.mark.parametrize("groups", [None, [0, 0, 1]])
+def test_load(pba, groups, zbuffer):
+    """Larger images, as many keyframes: the old poses, pairs and work queue do not serve the new set, neither after the
+    failure nor after a second attempt that succeeds."""
+    n = 3
+    with _loaded(pba, LARGE, n, occlusion_zbuffer=zbuffer) as ctx:
+        want = ctx.evaluate(want_system=True)
+    k = 0
+    while True:
+        with _loaded(pba, SMALL, n, groups, occlusion_zbuffer=zbuffer) as ctx:
+            ctx.evaluate()
+            load = lambda: ctx.load_keyframes([LARGE] * n, *_images(LARGE, n), None)
+            if not _out_of_memory(pba, load, k):
+                break
+            for call in (ctx.evaluate, lambda: ctx.iterate(1), lambda: ctx.loss_forward(np.zeros((n, 6), np.float32)),
+                         lambda: ctx.build_pyramid(2), lambda: ctx.set_pairs(PAIRS), ctx.get_poses, ctx.autotune):
+                _refused(pba, call)
+            load()
+            for call in (ctx.evaluate, lambda: ctx.iterate(1), ctx.get_poses):
+                _refused(pba, call)
+            ctx.set_poses(_poses(n))
+            _refused(pba, ctx.evaluate)
+            ctx.set_pairs(PAIRS)
+            _equal(ctx.evaluate(want_system=True), want)
+        k += 1
+    assert k >= 3
+
+
+def test_load_of_fewer_keyframes(pba):
+    k = 0
+    while True:
+        with _loaded(pba, SMALL, 4) as ctx:
+            if not _out_of_memory(pba, lambda: ctx.load_keyframes([LARGE] * 2, *_images(LARGE, 2), None), k):
+                break
+            _refused(pba, lambda: ctx.get_level_image(0, 3), pba.PBA_EINVAL)
+            _refused(pba, lambda: ctx.set_pose_groups([0, 0, 1, 1]))
+            _refused(pba, ctx.evaluate)
+        k += 1
+    assert k >= 1
+
+
+def test_new_images_of_the_same_set_from_a_pyramid_level(pba):
+    """Host images are staged: without memory for that, the set is given up, whatever level was active."""
+    n = 2
+    images = _images(LARGE, n, seed=1)
+    with _loaded(pba, LARGE, n) as ctx:
+        ctx.load_keyframes([LARGE] * n, *images, None)
+        want = ctx.evaluate(want_system=True)
+    k = 0
+    while True:
+        with _loaded(pba, LARGE, n) as ctx:
+            ctx.build_pyramid(2)
+            ctx.set_level(1)
+            ctx.iterate(1)
+            load = lambda: ctx.load_keyframes([LARGE] * n, *images, None)
+            if not _out_of_memory(pba, load, k):
+                break
+            _refused(pba, ctx.evaluate)
+            load()
+            ctx.set_poses(_poses(n))
+            ctx.set_pairs(PAIRS)
+            _equal(ctx.evaluate(want_system=True), want)
+        k += 1
+    assert k >= 1
+
+
+def test_a_refused_load_changes_nothing(pba):
+    """Two keyframes where the anchor is the third: refused before anything is given up."""
+    with _loaded(pba, SMALL, 3, anchor=2) as ctx:
+        want = ctx.evaluate(want_system=True)
+        _refused(pba, lambda: ctx.load_keyframes([LARGE] * 2, *_images(LARGE, 2), None), pba.PBA_EINVAL)
+        _equal(ctx.evaluate(want_system=True), want)
