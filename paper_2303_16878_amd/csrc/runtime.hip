@@ -74,6 +74,7 @@ struct pba_ctx {
     int items_px = 4096;    // source pixels per work item (one wave's)
     int tuned_px = 0;       // the size pba_autotune chose, 0 before any
     int n_items = 0;
+    bool queue_ok = false;  // the work queue is complete and the active level's
     struct Group { int sm, tm, base, count; };
     std::vector<Group> groups;
     std::vector<int32_t> pair_item_begin, pair_item_count;
@@ -486,6 +487,7 @@ int default_items_px(pba_ctx *c, const std::vector<int32_t> &src, const std::vec
 pba_status build_items(pba_ctx *c, const std::vector<int32_t> &src, const std::vector<int32_t> &tgt)
 {
     drop_graph(c);
+    c->queue_ok = false;
     const int P = (int)src.size();
     c->full_grid = false;
     c->items_px = c->tuned_px ? c->tuned_px : default_items_px(c, src, tgt);
@@ -559,6 +561,7 @@ pba_status build_items(pba_ctx *c, const std::vector<int32_t> &src, const std::v
         if ((s = ensure(c, c->zbuf, (size_t)(tot + 2) * 4))) return s;   // whole doubles for the fill
         c->zcells = tot;
     }
+    c->queue_ok = true;
     return PBA_OK;
 }
 
@@ -793,6 +796,10 @@ pba_status check_ready(pba_ctx *c)
     if (c->N == 0) return fail(c, PBA_ESTATE, "no keyframes loaded");
     if (!c->poses_set) return fail(c, PBA_ESTATE, "poses not set");
     if (c->P == 0) return fail(c, PBA_ESTATE, "pairs not set");
+    if (!c->queue_ok) {   // a level switch that ran out of memory left none
+        HIP_OK(hipSetDevice(c->cfg.device));
+        return build_items(c, c->src_h, c->tgt_h);
+    }
     return PBA_OK;
 }
 
@@ -1512,6 +1519,8 @@ pba_status pba_estimate_normals(pba_ctx *c, double radius_m, double min_px, doub
         c->lv.resize(1);
         if (c->level != 0) {
             c->level = 0;
+            c->system_valid = false;
+            c->loss_ready = false;
             if (c->P > 0 && (s = build_items(c, c->src_h, c->tgt_h))) return s;
         }
     }

@@ -171,3 +171,46 @@ def test_a_refused_load_changes_nothing(pba):
         want = ctx.evaluate(want_system=True)
         _refused(pba, lambda: ctx.load_keyframes([LARGE] * 2, *_images(LARGE, 2), None), pba.PBA_EINVAL)
         _equal(ctx.evaluate(want_system=True), want)
+
+
+@pytest.mark.parametrize("zbuffer", [False, True])
+@pytest.mark.parametrize("back", ["set_level", "estimate_normals"])
+def test_level_switch(pba, back, zbuffer):
+    """A switch to a finer level without memory for its longer queue: the next call that needs the queue builds it,
+    or reports that it cannot either."""
+    n, rng = 2, np.random.default_rng(5)
+    I, D = _images(LARGE, n)
+    N = [rng.standard_normal(i.shape + (3,)).astype(np.float32) for i in I]
+
+    def at_level_1():
+        ctx = pba.Context(occlusion_zbuffer=zbuffer)
+        H, W = SIZES[LARGE]
+        ctx.add_sensor(0, H, W, 0.8 * W, 0.8 * W, (W - 1) / 2, (H - 1) / 2, 0.1, 10.0)
+        ctx.load_keyframes([0] * n, I, D, N)
+        ctx.set_poses(_poses(n))
+        ctx.build_pyramid(2)
+        ctx.set_level(1)
+        ctx.set_pairs(PAIRS)
+        return ctx
+
+    switch = (lambda ctx: ctx.set_level(0)) if back == "set_level" else (lambda ctx: ctx.estimate_normals())
+    with at_level_1() as ctx:
+        switch(ctx)
+        want = ctx.evaluate(want_system=True)
+        want_log = ctx.iterate(2)
+    k = 0
+    while True:
+        with at_level_1() as ctx:
+            ctx.evaluate()
+            if not _out_of_memory(pba, lambda: switch(ctx), k):
+                break
+            with memory_for(0):
+                _refused(pba, ctx.evaluate, pba.PBA_ENOMEM)
+                _refused(pba, lambda: ctx.iterate(1), pba.PBA_ENOMEM)
+            ctx.set_level(0)
+            if back == "estimate_normals":
+                ctx.estimate_normals()
+            _equal(ctx.evaluate(want_system=True), want)
+            assert [dict(r, ms=0) for r in ctx.iterate(2)] == [dict(r, ms=0) for r in want_log]
+        k += 1
+    assert k >= 1
