@@ -36,8 +36,9 @@
  * Errors: every call returns a pba_status; no C++ exception crosses the ABI.
  * On error the context state is unchanged and pba_last_error() describes it; but a
  * pba_load_keyframes that runs out of device memory (PBA_ENOMEM) or meets a device
- * error leaves no keyframes loaded (PBA_ESTATE from what needs them until a load
- * succeeds).
+ * error leaves no keyframes loaded, and a pba_set_pairs, pba_set_pose_groups or
+ * pba_build_pairs that does leaves no pairs (PBA_ESTATE from what needs them until
+ * they are given again).
  *
  * Streams: work is ordered on the stream given in pba_config (a borrowed
  * hipStream_t; NULL = the null stream).  Calls that return host values

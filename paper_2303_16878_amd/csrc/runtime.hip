@@ -1136,20 +1136,26 @@ pba_status pba_set_pose_groups(pba_ctx *c, const int32_t *pose_of, int32_t n_pos
     c->NP = np;
     c->chol.rows = nullptr;
     pba_status s;
-    for (ImageSet &is : c->lv) {
-        for (int k = 0; k < c->N; ++k) is.kfs_h[k].pose = pose_var(c, k);
-        if ((s = upload(c, is.kfs_d, is.kfs_h.data(), is.kfs_h.size() * sizeof(KfDev)))) return s;
-    }
     drop_graph(c);
     c->poses_set = false;
     c->system_valid = false;
     c->loss_ready = false;
     c->lam_carry = -1.0;
-    if (c->P > 0) {
+    const int P = c->P;
+    c->P = 0;   // no pairs until their plan for the new variables is complete
+    for (ImageSet &is : c->lv) {
+        for (int k = 0; k < c->N; ++k) is.kfs_h[k].pose = pose_var(c, k);
+        if ((s = upload(c, is.kfs_d, is.kfs_h.data(), is.kfs_h.size() * sizeof(KfDev)))) {
+            drop_keyframes(c);   // (some levels name the new variables, some the old)
+            return s;
+        }
+    }
+    if (P > 0) {
         if ((s = build_plan(c, c->src_h, c->tgt_h))) return s;
         if ((s = ensure_system(c))) return s;
     }
     HIP_OK(hipStreamSynchronize(c->stream));
+    c->P = P;
     return PBA_OK;
 }
 
@@ -1165,6 +1171,11 @@ pba_status pba_set_pairs(pba_ctx *c, int32_t p, const int32_t *src, const int32_
     std::vector<int2> pr(p);
     for (int k = 0; k < p; ++k) pr[k] = make_int2(s[k], t[k]);
     drop_graph(c);
+    // no pairs until the new ones are complete
+    c->P = 0;
+    c->chol.rows = nullptr;
+    c->system_valid = false;
+    c->lam_carry = -1.0;
     pba_status st;
     if ((st = upload(c, c->pairs_d, pr.data(), pr.size() * sizeof(int2)))) return st;
     if ((st = build_plan(c, s, t))) return st;
@@ -1173,8 +1184,6 @@ pba_status pba_set_pairs(pba_ctx *c, int32_t p, const int32_t *src, const int32_
     c->src_h = s;
     c->tgt_h = t;
     c->P = p;
-    c->system_valid = false;
-    c->lam_carry = -1.0;
     return PBA_OK;
 }
 

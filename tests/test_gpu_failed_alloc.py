@@ -214,3 +214,60 @@ def test_level_switch(pba, back, zbuffer):
             assert [dict(r, ms=0) for r in ctx.iterate(2)] == [dict(r, ms=0) for r in want_log]
         k += 1
     assert k >= 1
+
+
+CHAIN = [(i, j) for i in range(30) for j in (i - 1, i + 1) if 0 <= j < 30]   # 30 poses: 180 rows, several blocks
+
+
+@pytest.mark.parametrize("zbuffer", [False, True])
+def test_set_pairs_and_build_pairs(pba, zbuffer):
+    """A longer pair list (its queue, assembly lists, factorisation plan or system do not fit): no pairs, neither the old
+    nor half of the new ones."""
+    n = 30
+    with _loaded(pba, SMALL, n, occlusion_zbuffer=zbuffer) as ctx:
+        ctx.set_pairs(CHAIN)
+        want = ctx.evaluate(want_system=True)
+        step = ctx.solve_step(1e-3)
+    for change in (lambda ctx: ctx.set_pairs(CHAIN),
+                   lambda ctx: ctx.build_pairs(max_angle=0.0, max_dist=0.0, min_ratio=0.0, sequential=True)):
+        k = 0
+        while True:
+            with _loaded(pba, SMALL, n, occlusion_zbuffer=zbuffer) as ctx:
+                ctx.evaluate()
+                if not _out_of_memory(pba, lambda: change(ctx), k):
+                    break
+                for call in (ctx.evaluate, lambda: ctx.solve_step(1e-3), lambda: ctx.iterate(1)):
+                    _refused(pba, call)
+                ctx.set_pairs(CHAIN)
+                _equal(ctx.evaluate(want_system=True), want)
+                assert np.array_equal(ctx.solve_step(1e-3), step)
+            k += 1
+        assert k >= 5
+
+
+def test_pose_groups(pba):
+    """More pose variables than before: no pairs until their plan is built."""
+    n, groups = 30, [k // 15 for k in range(30)]
+
+    def grouped():
+        ctx = _loaded(pba, SMALL, n, groups)
+        ctx.set_pairs(CHAIN)
+        return ctx
+
+    with _loaded(pba, SMALL, n) as ctx:
+        ctx.set_pairs(CHAIN)
+        want = ctx.evaluate(want_system=True)
+    k = 0
+    while True:
+        with grouped() as ctx:
+            ctx.evaluate()
+            if not _out_of_memory(pba, lambda: ctx.set_pose_groups(None), k):
+                break
+            ctx.n_poses = n
+            _refused(pba, ctx.evaluate)
+            ctx.set_poses(_poses(n))
+            _refused(pba, ctx.evaluate)
+            ctx.set_pairs(CHAIN)
+            _equal(ctx.evaluate(want_system=True), want)
+        k += 1
+    assert k >= 2
