@@ -1324,10 +1324,11 @@ pba_status pba_iterate(pba_ctx *c, int32_t n_iters, int32_t use_lm, double lambd
     if ((s = ensure_chol_plan(c))) return s;
     if (n_iters > c->log_cap) {
         const int cap = std::max(n_iters, 64);
+        drop_graph(c);   // the graph refers to the log buffer
         release(c->logbuf);
+        c->log_cap = 0;
         if ((s = ensure(c, c->logbuf, (size_t)cap * kLogRow * 8))) return s;
         c->log_cap = cap;
-        drop_graph(c);   // the graph refers to the log buffer
     }
     double *totals = P_<double>(c->totals);   // [0..3] current, [4..7] candidate
     // system at the current poses (reused if already evaluated there)

@@ -271,3 +271,16 @@ def test_pose_groups(pba):
             _equal(ctx.evaluate(want_system=True), want)
         k += 1
     assert k >= 2
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_iterate_without_memory_for_its_log(pba, graph):
+    with _loaded(pba, SMALL, 2, use_graph=graph) as ctx:
+        ctx.iterate(3)
+        want = [dict(r, ms=0) for r in ctx.iterate(3)]
+    with _loaded(pba, SMALL, 2, use_graph=graph) as ctx:
+        ctx.iterate(3)
+        assert _out_of_memory(pba, lambda: ctx.iterate(100), 0)
+        with memory_for(0):
+            _refused(pba, lambda: ctx.iterate(3), pba.PBA_ENOMEM)
+        assert [dict(r, ms=0) for r in ctx.iterate(3)] == want
