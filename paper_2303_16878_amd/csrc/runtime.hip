@@ -1677,6 +1677,7 @@ pba_status pba_build_pyramid(pba_ctx *c, int32_t n_levels)
             return fail(c, PBA_EINVAL, "level %d of a %d x %d sensor would be below 4 x 4", n_levels - 1, S.height,
                         S.width);
     HIP_OK(hipSetDevice(c->cfg.device));
+    if (c->level != 0) drop_graph(c);   // it refers to the planes released next
     for (size_t l = 1; l < c->lv.size(); ++l) release_images(c->lv[l]);
     c->lv.resize(n_levels);
     std::vector<int32_t> sensor_of(c->N);
