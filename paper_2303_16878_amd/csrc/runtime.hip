@@ -918,6 +918,42 @@ pba_status load_images(pba_ctx *c, const std::vector<int32_t> &sensor_of, const 
     return PBA_OK;
 }
 
+// Levels 1 .. n_levels - 1 from level 0 (pba_build_pyramid after its checks).
+pba_status reduce_levels(pba_ctx *c, int32_t n_levels)
+{
+    std::vector<int32_t> sensor_of(c->N);
+    for (int k = 0; k < c->N; ++k) sensor_of[k] = c->lv[0].kfs_h[k].sensor;
+    pba_status s;
+    for (int l = 1; l < n_levels; ++l) {
+        ImageSet &lo = c->lv[l - 1], &up = c->lv[l];
+        up.sensors = lo.sensors;
+        for (pba_sensor &S : up.sensors) {
+            S.height /= 2;
+            S.width /= 2;
+            S.fx /= 2.0;
+            S.fy /= 2.0;
+            S.cx = (S.cx - 0.5) / 2.0;
+            S.cy = (S.cy - 0.5) / 2.0;
+        }
+        if ((s = sensor_tables(c, up))) return s;
+        if ((s = image_layout(c, up, sensor_of))) return s;
+        const bool five = c->cfg.channels == 5;
+        for (int k = 0; k < c->N; ++k) {
+            const KfDev &a = lo.kfs_h[k], &b = up.kfs_h[k];
+            const double tau = lo.sensors[a.sensor].model == PBA_PINHOLE ? c->cfg.occlusion_tau_pinhole
+                                                                          : c->cfg.occlusion_tau_spherical;
+            launch_downsample(P_<float>(lo.dep) + a.off,
+                              static_cast<char *>(att_plane(c, lo)) + a.off * att_bytes(c), five ? 1 : 0,
+                              c->cfg.storage_bf16, a.H, a.W, P_<float>(up.dep) + b.off,
+                              static_cast<char *>(att_plane(c, up)) + b.off * att_bytes(c), b.H, b.W, tau, c->stream);
+        }
+        build_gate(c, up);
+        HIP_OK(hipGetLastError());
+    }
+    HIP_OK(hipStreamSynchronize(c->stream));
+    return PBA_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1680,36 +1716,19 @@ pba_status pba_build_pyramid(pba_ctx *c, int32_t n_levels)
     if (c->level != 0) drop_graph(c);   // it refers to the planes released next
     for (size_t l = 1; l < c->lv.size(); ++l) release_images(c->lv[l]);
     c->lv.resize(n_levels);
-    std::vector<int32_t> sensor_of(c->N);
-    for (int k = 0; k < c->N; ++k) sensor_of[k] = c->lv[0].kfs_h[k].sensor;
-    pba_status s;
-    for (int l = 1; l < n_levels; ++l) {
-        ImageSet &lo = c->lv[l - 1], &up = c->lv[l];
-        up.sensors = lo.sensors;
-        for (pba_sensor &S : up.sensors) {
-            S.height /= 2;
-            S.width /= 2;
-            S.fx /= 2.0;
-            S.fy /= 2.0;
-            S.cx = (S.cx - 0.5) / 2.0;
-            S.cy = (S.cy - 0.5) / 2.0;
+    const pba_status s = reduce_levels(c, n_levels);
+    if (s) {   // no level that is not complete: the loaded images alone remain, and are active
+        for (size_t l = 1; l < c->lv.size(); ++l) release_images(c->lv[l]);
+        c->lv.resize(1);
+        if (c->level != 0) {
+            c->level = 0;
+            c->queue_ok = false;
+            c->system_valid = false;
+            c->loss_ready = false;
+            c->lam_carry = -1.0;
         }
-        if ((s = sensor_tables(c, up))) return s;
-        if ((s = image_layout(c, up, sensor_of))) return s;
-        const bool five = c->cfg.channels == 5;
-        for (int k = 0; k < c->N; ++k) {
-            const KfDev &a = lo.kfs_h[k], &b = up.kfs_h[k];
-            const double tau = lo.sensors[a.sensor].model == PBA_PINHOLE ? c->cfg.occlusion_tau_pinhole
-                                                                          : c->cfg.occlusion_tau_spherical;
-            launch_downsample(P_<float>(lo.dep) + a.off,
-                              static_cast<char *>(att_plane(c, lo)) + a.off * att_bytes(c), five ? 1 : 0,
-                              c->cfg.storage_bf16, a.H, a.W, P_<float>(up.dep) + b.off,
-                              static_cast<char *>(att_plane(c, up)) + b.off * att_bytes(c), b.H, b.W, tau, c->stream);
-        }
-        build_gate(c, up);
-        HIP_OK(hipGetLastError());
+        return s;
     }
-    HIP_OK(hipStreamSynchronize(c->stream));
     if (c->level >= n_levels) return pba_set_level(c, 0);
     return PBA_OK;
 }

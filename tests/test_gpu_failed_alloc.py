@@ -284,3 +284,30 @@ def test_iterate_without_memory_for_its_log(pba, graph):
         with memory_for(0):
             _refused(pba, lambda: ctx.iterate(3), pba.PBA_ENOMEM)
         assert [dict(r, ms=0) for r in ctx.iterate(3)] == want
+
+
+@pytest.mark.parametrize("active", [0, 1])
+def test_pyramid(pba, active):
+    """A pyramid that does not fit: no level of it exists, the loaded images are active."""
+    with _loaded(pba, LARGE, 2) as ctx:
+        want = ctx.evaluate(want_system=True)
+        ctx.build_pyramid(3)
+        images = ctx.get_level_image(2, 1)
+    k = 0
+    while True:
+        with _loaded(pba, LARGE, 2) as ctx:
+            if active:
+                ctx.build_pyramid(2)
+                ctx.set_level(1)
+                ctx.evaluate()
+            if not _out_of_memory(pba, lambda: ctx.build_pyramid(3), k):
+                break
+            for level in (1, 2):
+                _refused(pba, lambda: ctx.set_level(level), pba.PBA_EINVAL)
+                _refused(pba, lambda: ctx.get_level_image(level, 0), pba.PBA_EINVAL)
+            _equal(ctx.evaluate(want_system=True), want)
+            assert len(ctx.optimize_pyramid([1])) == 1
+            ctx.build_pyramid(3)
+            assert all(np.array_equal(a, b) for a, b in zip(ctx.get_level_image(2, 1), images))
+        k += 1
+    assert k >= 10
