@@ -323,9 +323,12 @@ typedef struct {
 
 /* Autotuner of the persistent evaluation launch (work-item size and grid): times one evaluation
  * at the current poses and level for every item size in {512, ..., 16384} (powers of 2; the source
- * pixels one wave takes at a time) and grid in {2, 4, 8} x (compute units) workgroups, keeps the
- * fastest for this context (until keyframes or pairs change the plan again) and reports the
- * measured points (points nullable, up to max_points; *n_points nullable).  Results of evaluations do not depend on the choice except in
+ * pixels one wave takes at a time) and grid in {2, 4, 8} x (compute units) workgroups, the default
+ * size and grid among them (a default size that is not in the list is measured in place of 16384;
+ * where the default takes every workgroup the chip holds, that is measured in place of 8 x at its
+ * size), and keeps the fastest for these keyframes and pairs at this level (the default again once
+ * they change, and at other levels).  Reports the measured points (18; points nullable, up to
+ * max_points; *n_points nullable).  Results of evaluations do not depend on the choice except in
  * the summation order of the per-pair sums. */
 pba_status pba_autotune(pba_ctx *ctx, pba_tune_point *points, int32_t max_points, int32_t *n_points);
 

@@ -72,7 +72,8 @@ struct pba_ctx {
 
     // items
     int items_px = 4096;    // source pixels per work item (one wave's)
-    int tuned_px = 0;       // the size pba_autotune chose, 0 before any
+    // what pba_autotune chose for the pairs as set, in force at the level it was measured at (0: the default is)
+    int tuned_px = 0, tuned_grid = 0, tuned_level = 0;
     int n_items = 0;
     bool queue_ok = false;  // the work queue is complete and the active level's
     struct Group { int sm, tm, base, count; };
@@ -107,7 +108,7 @@ struct pba_ctx {
     double wall_khz = 0.0;   // device wall-clock rate
     int64_t eval_launches = 0, iterations = 0;
     int grid = 0;
-    bool full_grid = false;   // launches take every workgroup the chip holds of their kernel, at least `grid`
+    int full_grid = 0;   // launches take every workgroup the chip holds of their kernel, at least `grid`: that many (0: off)
 };
 
 namespace {
@@ -470,7 +471,7 @@ int default_items_px(pba_ctx *c, const std::vector<int32_t> &src, const std::vec
     const int per_cu = launch_eval(make_args(c), c->cfg.precision, c->cfg.channels, c->cfg.grad_mode, k >> 1, k & 1, false,
                                    0, 0, 0, c->stream);
     const int64_t full = std::max<int64_t>(1, (int64_t)per_cu * c->num_cu) * (kBlock / 64);
-    c->full_grid = px[k] >= 1024 * full;
+    c->full_grid = px[k] >= 1024 * full ? std::max(per_cu, 4) * c->num_cu : 0;
     const int64_t waves = c->full_grid ? full : std::min<int64_t>(full, (int64_t)c->grid * (kBlock / 64));
     const int64_t size = std::min<int64_t>(4096, std::max<int64_t>(64, ((px[k] + waves - 1) / waves + 63) / 64 * 64));
     // (a queue that the allocation-free evaluation's array holds in items of 4096 stays one)
@@ -489,8 +490,10 @@ pba_status build_items(pba_ctx *c, const std::vector<int32_t> &src, const std::v
     drop_graph(c);
     c->queue_ok = false;
     const int P = (int)src.size();
-    c->full_grid = false;
-    c->items_px = c->tuned_px ? c->tuned_px : default_items_px(c, src, tgt);
+    const bool tuned = c->tuned_px && c->tuned_level == c->level;
+    c->full_grid = 0;
+    c->grid = tuned ? c->tuned_grid : 4 * c->num_cu;
+    c->items_px = tuned ? c->tuned_px : default_items_px(c, src, tgt);
     // work items: (pair, first source pixel); grouped by (source model, target model),
     // ordered by target keyframe so items sharing a target image run close together
     std::vector<int> order(P);
@@ -834,6 +837,7 @@ void drop_keyframes(pba_ctx *c)
     c->lv.resize(1);
     c->level = 0;
     c->N = c->NP = c->P = 0;
+    c->tuned_px = 0;
     c->pose_of.clear();
     c->chol.rows = nullptr;
     c->poses_set = c->system_valid = c->loss_ready = false;
@@ -915,6 +919,49 @@ pba_status load_images(pba_ctx *c, const std::vector<int32_t> &sensor_of, const 
     if (same_layout) return prev_level != 0 && c->P > 0 ? build_items(c, c->src_h, c->tgt_h) : PBA_OK;
     c->N = n;
     c->NP = n;
+    return PBA_OK;
+}
+
+// Time the evaluation at each point of pba_autotune and leave the fastest in force.  The default is one of the points:
+// its size is one of the list or takes the place of the largest (a default below 4096 means that the load gives a
+// wave less than one item of 4096, so 16384 would leave most of them idle), and where it launches in full, that
+// takes the place of its largest grid.
+pba_status tune(pba_ctx *c, std::vector<pba_tune_point> &pts)
+{
+    pba_status s;
+    c->tuned_px = 0;
+    if ((s = build_items(c, c->src_h, c->tgt_h))) return s;
+    const int def_px = c->items_px, def_full = c->full_grid, def_grid = def_full ? def_full : c->grid;
+    int sizes[6] = {512, 1024, 2048, 4096, 8192, 16384};
+    if (std::find(sizes, sizes + 6, def_px) == sizes + 6) sizes[5] = def_px;
+    std::sort(sizes, sizes + 6);
+    pba_tune_point best{0, 0, 1e300};
+    for (int size : sizes) {
+        c->tuned_px = size;
+        c->tuned_grid = c->grid;
+        c->tuned_level = c->level;
+        if ((s = build_items(c, c->src_h, c->tgt_h))) return s;
+        for (int mult : {2, 4, 8}) {
+            const bool full = def_full && size == def_px && mult == 8;
+            c->full_grid = full ? def_full : 0;
+            c->grid = full ? 4 * c->num_cu : mult * c->num_cu;
+            double ms = 0.0;
+            for (int rep = 0; rep < 2; ++rep) {   // the first run warms caches and code
+                const double before = c->eval_ms;
+                if ((s = run_eval(c, P_<double>(c->poses), P_<double>(c->H_cand), P_<double>(c->b_cand),
+                                  P_<double>(c->totals) + 4, true, c->stream)))
+                    return s;
+                if ((s = accumulate_eval_time(c))) return s;
+                ms = c->eval_ms - before;
+            }
+            pts.push_back({size, full ? def_full : c->grid, ms});
+            if (ms < best.eval_ms) best = pts.back();
+        }
+    }
+    c->tuned_px = best.items_px == def_px && best.grid == def_grid ? 0 : best.items_px;
+    c->tuned_grid = best.grid;
+    if ((s = build_items(c, c->src_h, c->tgt_h))) return s;
+    HIP_OK(hipStreamSynchronize(c->stream));
     return PBA_OK;
 }
 
@@ -1209,6 +1256,7 @@ pba_status pba_set_pairs(pba_ctx *c, int32_t p, const int32_t *src, const int32_
     drop_graph(c);
     // no pairs until the new ones are complete
     c->P = 0;
+    c->tuned_px = 0;
     c->chol.rows = nullptr;
     c->system_valid = false;
     c->lam_carry = -1.0;
@@ -1633,6 +1681,7 @@ pba_status pba_build_pairs(pba_ctx *c, double max_angle, double max_dist, double
         std::vector<int2> pr(cs.size());
         for (size_t k = 0; k < cs.size(); ++k) pr[k] = make_int2(cs[k], ct[k]);
         c->P = 0;
+        c->tuned_px = 0;
         c->system_valid = false;
         c->lam_carry = -1.0;
         c->chol.rows = nullptr;
@@ -1671,35 +1720,15 @@ pba_status pba_autotune(pba_ctx *c, pba_tune_point *points, int32_t max_points, 
     pba_status s;
     if ((s = check_ready(c))) return s;
     HIP_OK(hipSetDevice(c->cfg.device));
-    const int sizes[6] = {512, 1024, 2048, 4096, 8192, 16384};
-    const int mult[3] = {2, 4, 8};
-    int best_px = c->items_px, best_grid = c->grid, n = 0;
-    double best = 1e300;
-    for (int si = 0; si < 6; ++si) {
-        c->tuned_px = sizes[si];
-        if ((s = build_items(c, c->src_h, c->tgt_h))) return s;
-        for (int gi = 0; gi < 3; ++gi) {
-            c->grid = c->num_cu * mult[gi];
-            double ms = 0.0;
-            for (int rep = 0; rep < 2; ++rep) {   // the first run warms caches and code
-                const double before = c->eval_ms;
-                if ((s = run_eval(c, P_<double>(c->poses), P_<double>(c->H_cand), P_<double>(c->b_cand),
-                                  P_<double>(c->totals) + 4, true, c->stream)))
-                    return s;
-                if ((s = accumulate_eval_time(c))) return s;
-                ms = c->eval_ms - before;
-            }
-            if (points && n < max_points) points[n] = pba_tune_point{sizes[si], c->grid, ms};
-            ++n;
-            if (ms < best) { best = ms; best_px = sizes[si]; best_grid = c->grid; }
-        }
+    std::vector<pba_tune_point> pts;
+    if ((s = tune(c, pts))) {
+        c->tuned_px = 0;
+        c->queue_ok = false;   // whatever point was being measured: the next call goes back to the default
+        return s;
     }
-    c->tuned_px = best_px;
-    c->grid = best_grid;
-    if ((s = build_items(c, c->src_h, c->tgt_h))) return s;
-    drop_graph(c);
-    HIP_OK(hipStreamSynchronize(c->stream));
-    if (n_points) *n_points = std::min(n, max_points);
+    const int n = std::min((int)pts.size(), max_points);
+    if (points) std::copy(pts.begin(), pts.begin() + n, points);
+    if (n_points) *n_points = n;
     return PBA_OK;
 }
 
@@ -1874,7 +1903,7 @@ pba_status pba_get_timings(pba_ctx *c, pba_timings *out, int32_t reset)
     out->iterations = c->iterations;
     out->n_items = c->n_items;
     out->items_px = c->items_px;
-    out->grid = c->grid;
+    out->grid = c->full_grid ? c->full_grid : c->grid;
     out->iter_eval_ms = c->iter_eval_ms;
     out->iter_evals = c->iter_evals;
     out->solve_n = c->chol.rows ? c->chol.n : 0;
