@@ -91,7 +91,7 @@ struct pba_ctx {
     int64_t zcells = 0;
     DevBuf H, b, H_cand, b_cand, totals, A, Winv, dx, lm, fail, logbuf;
     DevBuf dbg_status, dbg_uv, dbg_cell, dbg_res;
-    DevBuf kf_in, loss_delta, loss_poses, g_img, g_out, g_stage, g_pose;
+    DevBuf kf_in, loss_delta, loss_dx, loss_poses, g_img, g_out, g_stage, g_pose;
     bool loss_ready = false;
 
     // one captured LM iteration (replayed by pba_iterate)
@@ -1102,7 +1102,7 @@ pba_status pba_destroy(pba_ctx *c)
                       &c->counters, &c->partials, &c->pair_out, &c->blk_rc, &c->blk_ptr, &c->blk_ent, &c->bk_ptr,
                       &c->bk_ent, &c->H, &c->b, &c->H_cand, &c->b_cand, &c->totals, &c->A, &c->Winv, &c->dx, &c->lm,
                       &c->fail, &c->logbuf, &c->dbg_status, &c->dbg_uv, &c->dbg_cell, &c->dbg_res,
-                      &c->kf_in, &c->loss_delta, &c->loss_poses, &c->g_img, &c->g_out, &c->g_stage, &c->g_pose,
+                      &c->kf_in, &c->loss_delta, &c->loss_dx, &c->loss_poses, &c->g_img, &c->g_out, &c->g_stage, &c->g_pose,
                       &c->chol_rows, &c->chol_cols, &c->chol_meta, &c->zbuf, &c->zoff, &c->nd_perm,
                       &c->nd_off, &c->nd_dtiles, &c->nd_lcols, &c->nd_panels, &c->nd_tasks, &c->nd_contrib, &c->dx_nat};
     drop_graph(c);
@@ -1487,6 +1487,7 @@ pba_status pba_loss_forward(pba_ctx *c, const float *delta, int32_t on_device, d
     HIP_OK(hipSetDevice(c->cfg.device));
     const int N = c->NP;   // pose variables
     if ((s = ensure(c, c->loss_delta, (size_t)N * 6 * 4))) return s;
+    if ((s = ensure(c, c->loss_dx, (size_t)N * 6 * 8))) return s;
     if ((s = ensure(c, c->loss_poses, (size_t)N * 12 * 8))) return s;
     if (on_device) {
         HIP_OK(hipMemcpyAsync(c->loss_delta.p, delta, (size_t)N * 24, hipMemcpyDeviceToDevice, c->stream));
@@ -1495,9 +1496,9 @@ pba_status pba_loss_forward(pba_ctx *c, const float *delta, int32_t on_device, d
             if (!std::isfinite(delta[i])) return fail(c, PBA_EINVAL, "non-finite delta");
         HIP_OK(hipMemcpyAsync(c->loss_delta.p, delta, (size_t)N * 24, hipMemcpyHostToDevice, c->stream));
     }
-    // X = X0 boxplus delta (the step buffer is scratch here)
-    launch_delta_to_dx(P_<float>(c->loss_delta), P_<double>(c->dx), N, c->stream);
-    launch_boxplus(P_<double>(c->poses), P_<double>(c->dx), nullptr, P_<double>(c->loss_poses), N, c->stream);
+    // X = X0 boxplus delta
+    launch_delta_to_dx(P_<float>(c->loss_delta), P_<double>(c->loss_dx), N, c->stream);
+    launch_boxplus(P_<double>(c->poses), P_<double>(c->loss_dx), nullptr, P_<double>(c->loss_poses), N, c->stream);
     double *tot = P_<double>(c->totals) + 4;
     if ((s = run_eval(c, P_<double>(c->loss_poses), P_<double>(c->H_cand), P_<double>(c->b_cand), tot, false,
                       c->stream)))
