@@ -222,7 +222,9 @@ pba_status pba_evaluate_noalloc(pba_ctx *ctx, pba_eval_out *out);
  * pba_apply_step. */
 pba_status pba_solve_step(pba_ctx *ctx, double lambda, double *dx, int32_t on_device);
 
-/* X_k <- X_k exp(dx_k) for every pose; dx NULL applies the last solved step. */
+/* X_k <- X_k exp(dx_k) for every pose; dx NULL applies the last step solved (or given) for these
+ * keyframes, PBA_ESTATE if there is none (with a nested-dissection order also after the pairs were set
+ * again). */
 pba_status pba_apply_step(pba_ctx *ctx, const double *dx, int32_t on_device);
 
 typedef struct {

@@ -90,6 +90,8 @@ struct pba_ctx {
     DevBuf zbuf, zoff;   // z-buffer occlusion variant: per pair, one FP32 depth per target pixel
     int64_t zcells = 0;
     DevBuf H, b, H_cand, b_cand, totals, A, Winv, dx, lm, fail, logbuf;
+    // what dx holds: nothing, or the last step (solved or applied) in pose order or in the plan's dissection layout
+    enum { STEP_NONE, STEP_POSES, STEP_ND } step = STEP_NONE;
     DevBuf dbg_status, dbg_uv, dbg_cell, dbg_res;
     DevBuf kf_in, loss_delta, loss_dx, loss_poses, g_img, g_out, g_stage, g_pose;
     bool loss_ready = false;
@@ -433,6 +435,7 @@ pba_status build_chol_plan(pba_ctx *c, const std::vector<int32_t> &src, const st
     // their transposes; the inverted diagonal blocks (64 x 64 each, zero-padded) then their
     // transposes; the step
     const size_t nz = (size_t)n;
+    if (c->step == pba_ctx::STEP_ND || c->dx.bytes < nz * 8) c->step = pba_ctx::STEP_NONE;   // laid out for another plan, or released
     if ((s = ensure(c, c->A, 3 * nz * nz * 8))) return s;
     if ((s = ensure(c, c->Winv, 2 * (size_t)nt * 64 * 64 * 8))) return s;
     if ((s = ensure(c, c->dx, nz * 8))) return s;
@@ -838,6 +841,7 @@ void drop_keyframes(pba_ctx *c)
     c->level = 0;
     c->N = c->NP = c->P = 0;
     c->tuned_px = 0;
+    c->step = pba_ctx::STEP_NONE;
     c->pose_of.clear();
     c->chol.rows = nullptr;
     c->poses_set = c->system_valid = c->loss_ready = false;
@@ -1217,6 +1221,7 @@ pba_status pba_set_pose_groups(pba_ctx *c, const int32_t *pose_of, int32_t n_pos
     HIP_OK(hipSetDevice(c->cfg.device));
     c->pose_of = g;
     c->NP = np;
+    c->step = pba_ctx::STEP_NONE;
     c->chol.rows = nullptr;
     pba_status s;
     drop_graph(c);
@@ -1350,6 +1355,7 @@ pba_status pba_solve_step(pba_ctx *c, double lambda, double *dx, int32_t on_devi
         c->system_valid = true;
     }
     enqueue_solve(c, P_<LmState>(c->lm), lambda, Stamp{}, c->stream);
+    c->step = c->chol.nd ? pba_ctx::STEP_ND : pba_ctx::STEP_POSES;
     // the step in pose order
     const double *step = P_<double>(c->dx);
     if (c->chol.nd && dx) {
@@ -1385,9 +1391,13 @@ pba_status pba_apply_step(pba_ctx *c, const double *dx, int32_t on_device)
         }
         for (double v : h)
             if (!std::isfinite(v)) return fail(c, PBA_EINVAL, "non-finite step");
+        c->step = pba_ctx::STEP_NONE;
         if ((s = upload(c, c->dx, h.data(), (size_t)n * 8))) return s;
+        c->step = pba_ctx::STEP_POSES;
     }
-    launch_boxplus(P_<double>(c->poses), P_<double>(c->dx), nullptr, P_<double>(c->poses_cand), c->NP, c->stream);
+    if (c->step == pba_ctx::STEP_NONE) return fail(c, PBA_ESTATE, "no step solved for these keyframes and pairs");
+    launch_boxplus(P_<double>(c->poses), P_<double>(c->dx), c->step == pba_ctx::STEP_ND ? c->chol.pose_off : nullptr,
+                   P_<double>(c->poses_cand), c->NP, c->stream);
     launch_copy(P_<double>(c->poses), P_<double>(c->poses_cand), (int64_t)c->NP * 12, c->stream);
     HIP_OK(hipGetLastError());
     HIP_OK(hipStreamSynchronize(c->stream));
@@ -1425,6 +1435,7 @@ pba_status pba_iterate(pba_ctx *c, int32_t n_iters, int32_t use_lm, double lambd
                    use_lm ? (lambda0 > 0.0 ? lambda0 : (c->lam_carry > 0.0 ? c->lam_carry : 1e-4)) : 0.0, use_lm ? 1 : 0,
                    c->stream);
     HIP_OK(hipEventRecord(c->ev0, c->stream));
+    c->step = c->chol.nd ? pba_ctx::STEP_ND : pba_ctx::STEP_POSES;
     if (c->cfg.use_graph) {
         if (!c->graph_valid) {
             if (!c->cap_stream) HIP_OK(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
