@@ -832,6 +832,18 @@ pba_status ensure_system(pba_ctx *c)
     return PBA_OK;
 }
 
+// Whether p is memory of the context's device, which its kernels may write to (that of another device, or of the host,
+// takes a copy: peers need not be mapped).
+bool own_memory(const pba_ctx *c, const void *p)
+{
+    hipPointerAttribute_t at;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();   // unknown to the runtime
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == c->cfg.device;
+}
+
 // The keyframes and all that follows from them given up: the context is as before its first load (the sensors stay).
 void drop_keyframes(pba_ctx *c)
 {
@@ -1561,51 +1573,50 @@ pba_status pba_loss_backward(pba_ctx *c, double grad_F, float *grad_delta, float
     launch_assemble(P_<double>(c->pair_out), c->P, P_<int2>(c->blk_rc), P_<int32_t>(c->blk_ptr),
                     P_<int32_t>(c->blk_ent), c->nblk, P_<int32_t>(c->bk_ptr), P_<int32_t>(c->bk_ent), N,
                     P_<double>(c->H_cand), P_<double>(c->b_cand), P_<double>(c->totals) + 4, nullptr, c->stream);
-    launch_pose_grad(P_<double>(c->b_cand), P_<float>(c->loss_delta), grad_F,
-                     on_device && grad_delta ? grad_delta : P_<float>(c->g_pose), N, c->stream);
-    HIP_OK(hipGetLastError());
-    if (!on_device && grad_delta)
-        HIP_OK(hipMemcpyAsync(grad_delta, c->g_pose.p, (size_t)N * 24, hipMemcpyDeviceToHost, c->stream));
-    // every keyframe's image gradients (pose variables may be shared): device outputs in one launch; for host
-    // outputs the launch only interleaves the normals, and each array is copied
+    // outputs on the context's device are written in one launch for all keyframes (pose variables may be shared); for
+    // others the launch only interleaves the normals, and each array is copied
     const std::vector<KfDev> &kfs = c->L().kfs_h;
     std::vector<GradOut> outs;
-    int max_px = 0;
-    if (!on_device && five && grad_normals && (s = ensure(c, c->g_stage, (size_t)tx * 12))) return s;
+    bool direct = on_device && (!grad_delta || own_memory(c, grad_delta));
     for (int k = 0; k < c->N; ++k) {
-        GradOut o{};
-        o.off = kfs[k].off;
-        o.npx = kfs[k].H * kfs[k].W;
-        if (on_device) {
-            o.gi = grad_intensity ? grad_intensity[k] : nullptr;
-            o.gd = grad_depth ? grad_depth[k] : nullptr;
-            o.gn = five && grad_normals ? grad_normals[k] : nullptr;
-        } else if (five && grad_normals && grad_normals[k]) {
+        const GradOut o{grad_intensity ? grad_intensity[k] : nullptr, grad_depth ? grad_depth[k] : nullptr,
+                        five && grad_normals ? grad_normals[k] : nullptr, kfs[k].off, kfs[k].H * kfs[k].W, 0};
+        for (const float *p : {o.gi, o.gd, o.gn}) direct = direct && (!p || own_memory(c, p));
+        if (o.gi || o.gd || o.gn) outs.push_back(o);
+    }
+    float *const g_pose = direct && grad_delta ? grad_delta : P_<float>(c->g_pose);
+    launch_pose_grad(P_<double>(c->b_cand), P_<float>(c->loss_delta), grad_F, g_pose, N, c->stream);
+    HIP_OK(hipGetLastError());
+    const hipMemcpyKind kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
+    if (grad_delta && g_pose != grad_delta)
+        HIP_OK(hipMemcpyAsync(grad_delta, c->g_pose.p, (size_t)N * 24, kind, c->stream));
+    if (!direct && five && grad_normals && (s = ensure(c, c->g_stage, (size_t)tx * 12))) return s;
+    std::vector<GradOut> launch;
+    int max_px = 0;
+    for (GradOut o : outs) {
+        if (!direct) {
+            if (!o.gn) continue;
+            o.gi = o.gd = nullptr;
             o.gn = P_<float>(c->g_stage) + 3 * o.off;
         }
-        if (!o.gi && !o.gd && !o.gn) continue;
         max_px = std::max(max_px, o.npx);
-        outs.push_back(o);
+        launch.push_back(o);
     }
-    if (!outs.empty()) {
-        if ((s = upload(c, c->g_out, outs.data(), outs.size() * sizeof(GradOut)))) return s;
-        for (size_t k = 0; k < outs.size(); k += 32768) {   // (a grid's y extent is at most 65535)
-            const int n = (int)std::min<size_t>(32768, outs.size() - k);
+    if (!launch.empty()) {
+        if ((s = upload(c, c->g_out, launch.data(), launch.size() * sizeof(GradOut)))) return s;
+        for (size_t k = 0; k < launch.size(); k += 32768) {   // (a grid's y extent is at most 65535)
+            const int n = (int)std::min<size_t>(32768, launch.size() - k);
             launch_grad_out(P_<float>(c->g_img), plane, P_<GradOut>(c->g_out) + k, n, max_px, c->stream);
         }
         HIP_OK(hipGetLastError());
     }
-    for (int k = 0; k < c->N && !on_device; ++k) {
-        const size_t npx = (size_t)kfs[k].H * kfs[k].W;
-        const int64_t off = kfs[k].off;
-        const float *g = P_<float>(c->g_img) + off;
-        if (grad_intensity && grad_intensity[k])
-            HIP_OK(hipMemcpyAsync(grad_intensity[k], g, npx * 4, hipMemcpyDeviceToHost, c->stream));
-        if (grad_depth && grad_depth[k])
-            HIP_OK(hipMemcpyAsync(grad_depth[k], g + plane, npx * 4, hipMemcpyDeviceToHost, c->stream));
-        if (five && grad_normals && grad_normals[k])
-            HIP_OK(hipMemcpyAsync(grad_normals[k], P_<float>(c->g_stage) + 3 * off, npx * 12, hipMemcpyDeviceToHost,
-                                  c->stream));
+    for (const GradOut &o : outs) {
+        if (direct) break;
+        const size_t npx = o.npx;
+        const float *g = P_<float>(c->g_img) + o.off;
+        if (o.gi) HIP_OK(hipMemcpyAsync(o.gi, g, npx * 4, kind, c->stream));
+        if (o.gd) HIP_OK(hipMemcpyAsync(o.gd, g + plane, npx * 4, kind, c->stream));
+        if (o.gn) HIP_OK(hipMemcpyAsync(o.gn, P_<float>(c->g_stage) + 3 * o.off, npx * 12, kind, c->stream));
     }
     HIP_OK(hipStreamSynchronize(c->stream));
     return PBA_OK;
