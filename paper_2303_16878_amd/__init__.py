@@ -266,6 +266,7 @@ class Context:
         self.p = 0
         self.sensor_sizes = []
         self.kf_sensor = None
+        self._loaded = None     # the sensors of the set that is loaded
 
     def _check(self, st, ctx="self"):
         if st != PBA_OK:
@@ -321,13 +322,17 @@ class Context:
                     raise ValueError("mixing host and device images")
             ptrs[name] = ps
         sid = np.ascontiguousarray(sensor_ids, np.int32)
-        self._check(self.lib.pba_load_keyframes(
+        st = self.lib.pba_load_keyframes(
             self.h, n, sid.ctypes.data, ctypes.cast(ptrs["I"], ctypes.c_void_p),
             ctypes.cast(ptrs["D"], ctypes.c_void_p),
-            ctypes.cast(ptrs["N"], ctypes.c_void_p) if ptrs["N"] is not None else None, int(on_dev or 0)))
+            ctypes.cast(ptrs["N"], ctypes.c_void_p) if ptrs["N"] is not None else None, int(on_dev or 0))
+        if st in (PBA_ENOMEM, PBA_EDEVICE):
+            self._loaded = None     # no keyframes are left
+        self._check(st)
+        if self._loaded is None or not np.array_equal(self._loaded, sid):
+            self.n_poses = n        # a new set has one pose per keyframe; new images of the set keep its grouping
         self.n = n
-        self.n_poses = n
-        self.kf_sensor = sid.copy()
+        self.kf_sensor = self._loaded = sid.copy()
 
     def set_poses(self, poses):
         p, dev, ka = _ptr(poses, np.float64)
