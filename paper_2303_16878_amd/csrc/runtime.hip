@@ -453,16 +453,20 @@ pba_status ensure_chol_plan(pba_ctx *c)
 
 EvalArgs make_args(pba_ctx *c);
 
-// Source pixels per work item, unless tuned: 4096, or the smallest multiple of 64 that gives every wave the
-// chip holds (of the launch's grid) at most one item of the largest model group.  Above one item per wave the
-// queue and the ends of items (about 1100 instructions and a partial batch each) cost more than finer items
-// balance: 7000 pairs of 64x1024 take 3.66 ms in items of 4096, 4.41 in items of 2048.  Below, waves without
-// an item idle: 20 pairs of 120x160 take 85 / 17 / 13 us in items of 4096 / 512 / 128, 56 pairs of 240x320
-// 135 / 75 us in items of 4096 / 1024.
-// Two cues between pinhole sensors (FP32) fit six waves to a SIMD where the grid holds four.  They are launched in
-// full where every wave gets 1024 pixels or more (full_grid): 1000 pairs of 480x640 take 7.0 ms for three
-// evaluations and two steps, 7.5 on the grid; 180 of 240x320 1.48, 1.55 for five steps.  With less, the ends of the
-// smaller items cost more than the waves give: ten steps of 20 pairs of 120x160 take 646 us so, 598 on the grid.
+// Source pixels per work item, unless tuned: 4096, or the smallest multiple of 64 at which the largest model group's
+// pixels make one item for every wave the chip holds (of the launch's grid); the ragged last item of each pair can
+// make a few more.  Above one item per wave the queue and the ends of items (about 1100 instructions and a partial
+// batch each) cost more than finer items balance: 7000 pairs of 64x1024 take 3.66 ms in items of 4096, 4.41 in items
+// of 2048.  Below, waves without an item idle: 20 pairs of 120x160 take 85 / 17 / 13 us in items of 4096 / 512 / 128,
+// 56 pairs of 240x320 135 / 75 us in items of 4096 / 1024.
+// The grid holds four workgroups per compute unit, one wave of each per SIMD.  Where the largest group's kernel lets
+// every wave that fits have 1024 pixels or more, the evaluation is launched in full instead, each group as its
+// kernel fits (full_grid): FP32 with two cues, six between pinhole sensors and five from spherical into pinhole ones;
+// every other kernel fits four or fewer, for which both are the same.  Between pinhole sensors, 1000 pairs of 480x640
+// take 7.0 ms for three evaluations and two steps, 7.5 on the grid; 180 of 240x320 1.48, 1.55 for five steps; from
+// spherical into pinhole, 465 pairs of 64x512 81 us an evaluation, 88, and 1245 190, 202.  With less, the ends of the
+// smaller items cost more than the waves give: ten steps of 20 pairs of 120x160 take 646 us so, 598 on the grid.  The
+// z-buffer pass and the loss adjoint run the same items on the grid.
 int default_items_px(pba_ctx *c, const std::vector<int32_t> &src, const std::vector<int32_t> &tgt)
 {
     int64_t px[4] = {0, 0, 0, 0};
