@@ -402,7 +402,7 @@ pba_status build_chol_plan(pba_ctx *c, const std::vector<int32_t> &src, const st
     pl.np = np;
     pl.n = n;
     pl.nd = nd;
-    const NdArrays a = nd_arrays(tp, pos);
+    NdArrays a = nd_arrays(tp, pos);
     pl.lbeg = a.lbeg;
     pl.lcnt = a.lcnt;
     pl.pbeg = a.pbeg;
@@ -410,12 +410,11 @@ pba_status build_chol_plan(pba_ctx *c, const std::vector<int32_t> &src, const st
     pl.tbeg = a.tbeg;
     pl.tcnt = a.tcnt;
     pl.ndt = 0;
-    std::vector<int32_t> panels = a.panels, tasks = a.tasks, contrib = a.contrib;
-    contrib.push_back(0);   // keep the device arrays non-empty
-    tasks.insert(tasks.end(), {0, 0, 0, 0});
-    if ((s = upload(c, c->nd_panels, panels.data(), panels.size() * 4))) return s;
-    if ((s = upload(c, c->nd_tasks, tasks.data(), tasks.size() * 4))) return s;
-    if ((s = upload(c, c->nd_contrib, contrib.data(), contrib.size() * 4))) return s;
+    a.contrib.push_back(0);   // keep the device arrays non-empty
+    a.tasks.insert(a.tasks.end(), {0, 0, 0, 0});
+    if ((s = upload(c, c->nd_panels, a.panels.data(), a.panels.size() * 4))) return s;
+    if ((s = upload(c, c->nd_tasks, a.tasks.data(), a.tasks.size() * 4))) return s;
+    if ((s = upload(c, c->nd_contrib, a.contrib.data(), a.contrib.size() * 4))) return s;
     pl.panels = P_<int32_t>(c->nd_panels);
     pl.tasks = P_<int32_t>(c->nd_tasks);
     pl.contrib = P_<int32_t>(c->nd_contrib);

@@ -65,13 +65,16 @@ int main(int argc, char **argv)
     std::vector<int> pos(np);
     for (int v = 0; v < np; ++v) pos[v] = 6 * v;
     if (nd) pos = nd_positions(np, nd_blocks(np, edges, 20), n);
+    auto now = [] { return std::chrono::steady_clock::now(); };
+    auto ms = [](auto d) { return std::chrono::duration<double>(d).count() * 1e3; };
+    const auto t0 = now();
     const TilePattern tp = tile_pattern(n, pos, edges);
-    const auto t0 = std::chrono::steady_clock::now();
+    const auto t1 = now();
     const NdArrays a = nd_arrays(tp, pos);
-    const double ms = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() * 1e3;
+    const auto t2 = now();
     const int nt = tp.nt, nlev = tp.nlev;
-    fprintf(stderr, "n %d nt %d levels %d tasks %zu panels %zu lists_ms %.3f\n", n, nt, nlev, a.tasks.size() / 4,
-            a.panels.size() / 2, ms);
+    fprintf(stderr, "n %d nt %d levels %d tasks %zu panels %zu pattern_ms %.4f lists_ms %.4f\n", n, nt, nlev,
+            a.tasks.size() / 4, a.panels.size() / 2, ms(t1 - t0), ms(t2 - t1));
     // the lists
     CHECK((int)a.pbeg.size() == nlev && (int)a.pcnt.size() == nlev && (int)a.tbeg.size() == nlev && (int)a.tcnt.size() == nlev);
     std::vector<int> contrib, tasks;

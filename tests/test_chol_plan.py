@@ -98,3 +98,13 @@ def test_lists_of_large_graphs(checker, N, order):
     if order == "natural":
         assert st["levels"] == nt == st["nt"]
         assert st["tasks"] > 0.8 * nt ** 3 / 6
+
+
+def test_lists_of_a_filled_order_take_no_longer_than_writing_them(checker):
+    """929770 tasks at 188 block columns: 20 bytes each against a byte written per tile of the symbolic fill, which makes
+    the same visits: some 12 times its time, where a sorted map of the tasks took 180 times."""
+    ratio = []
+    for _ in range(3):
+        _, st = _run(checker, "natural", 2000, _filled(2000), solve=False)
+        ratio.append(st["lists_ms"] / st["pattern_ms"])
+    assert min(ratio) < 60, ratio
