@@ -461,19 +461,9 @@ class Context:
         dims = np.zeros(2, np.int32)
         self._check(self.lib.pba_get_level_image(self.h, int(level), int(kf), None, None, None, dims.ctypes.data))
         H, W = int(dims[0]), int(dims[1])
-        if 20 * H * W >= 1 << 22:
-            # one block for the three images: one copy from the device, and an allocation of 4 MB or more is backed by
-            # large pages where the system has them (fresh 4 KB pages cost more than the copy into them): 653 us an
-            # image of 480x640, 979 as three arrays
-            block = np.empty(5 * H * W, np.float32)
-            I, D = block[:H * W].reshape(H, W), block[H * W:2 * H * W].reshape(H, W)
-            N = block[2 * H * W:].reshape(H, W, 3)
-        else:
-            # below, a block gets small pages as well: loading 17 images of 323x507, their normals and reading all back
-            # takes 7.2 ms with blocks, 5.6 with three arrays
-            I = np.empty((H, W), np.float32)
-            D = np.empty((H, W), np.float32)
-            N = np.empty((H, W, 3), np.float32)
+        I = np.empty((H, W), np.float32)
+        D = np.empty((H, W), np.float32)
+        N = np.empty((H, W, 3), np.float32)
         self._check(self.lib.pba_get_level_image(self.h, int(level), int(kf), I.ctypes.data, D.ctypes.data,
                                                  N.ctypes.data, None))
         return I, D, N

@@ -1864,11 +1864,6 @@ pba_status pba_get_level_image(pba_ctx *c, int32_t level, int32_t kf, float *int
     launch_unpack(P_<float>(is.dep) + f.off, static_cast<char *>(att_plane(c, is)) + f.off * att_bytes(c), five ? 1 : 0,
                   c->cfg.storage_bf16, (int)npx, I, D, five ? N : nullptr, c->stream);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess && five && intensity && depth == intensity + npx && normals == depth + npx) {
-        // outputs laid out like the staging buffer: one copy
-        e = hipMemcpyAsync(intensity, I, npx * 20, hipMemcpyDeviceToHost, c->stream);
-        intensity = depth = normals = nullptr;
-    }
     if (e == hipSuccess && intensity) e = hipMemcpyAsync(intensity, I, npx * 4, hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess && depth) e = hipMemcpyAsync(depth, D, npx * 4, hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess && normals) {
