@@ -357,8 +357,10 @@ typedef struct {
     int64_t iter_evals;
     int32_t solve_n;             /* order of the factored system (6 x pose variables, more with the
                                     padding of a nested-dissection order); 0 before the first plan */
-    int32_t solve_steps;         /* dependent steps of the factorisation: block columns (natural order)
-                                    or elimination-tree levels (nested dissection) */
+    int32_t solve_steps;         /* dependent steps of the solve: block columns (natural order, whose
+                                    triangular sweeps walk them one by one; its factorisation takes a step
+                                    per level of their elimination tree, as many unless parts of the order
+                                    are independent) or elimination-tree levels (nested dissection) */
     int32_t solve_nd;            /* 1 if the nested-dissection order is in use */
     int32_t reserved;
 } pba_timings;

@@ -822,7 +822,8 @@ __global__ void __launch_bounds__(kBlock)
                 // requests its atomics make (14 to 21 per ns), so every channel has a plane of its own (a wave's texels
                 // are nearly consecutive: normals three floats apart made three times the requests), and a lane
                 // whose right neighbour's cell is the next one hands it its two right taps by DPP: its left ones
-                // go there.  90 pairs of 240x320: 1139 -> 689 us.
+                // go there.  90 pairs of 240x320, five channels: 1349 us with normals three floats apart, 1139 with
+                // planes, 690 with the taps handed over as well.
                 const int base = y0 * Wt + x0;
                 const bool from_left = __builtin_amdgcn_update_dpp(-2, base, kDppShr1, 0xF, 0xF, false) + 1 == base;
                 const bool to_right = __builtin_amdgcn_update_dpp(-2, base, kDppShl1, 0xF, 0xF, false) == base + 1;

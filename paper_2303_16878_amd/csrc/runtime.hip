@@ -463,9 +463,10 @@ EvalArgs make_args(pba_ctx *c);
 // kernel fits (full_grid): FP32 with two cues, six between pinhole sensors and five from spherical into pinhole ones;
 // every other kernel fits four or fewer, for which both are the same.  Between pinhole sensors, 1000 pairs of 480x640
 // take 7.0 ms for three evaluations and two steps, 7.5 on the grid; 180 of 240x320 1.48, 1.55 for five steps; from
-// spherical into pinhole, 465 pairs of 64x512 81 us an evaluation, 88, and 1245 190, 202.  With less, the ends of the
-// smaller items cost more than the waves give: ten steps of 20 pairs of 120x160 take 646 us so, 598 on the grid.  The
-// z-buffer pass and the loss adjoint run the same items on the grid.
+// spherical into pinhole, 465 pairs of 64x512 81 us an evaluation, 88, and 1245 190, 202 (but 180 pairs, whose ragged
+// items are 5220 for 5120 waves, 50, 42).  With less, the ends of the smaller items cost more than the waves give: ten
+// steps of 20 pairs of 120x160 take 646 us so, 598 on the grid.  The z-buffer pass and the loss adjoint run the same
+// items on the grid.
 int default_items_px(pba_ctx *c, const std::vector<int32_t> &src, const std::vector<int32_t> &tgt)
 {
     int64_t px[4] = {0, 0, 0, 0};
