@@ -801,12 +801,13 @@ size_t att_bytes(const pba_ctx *c)
     return c->cfg.storage_bf16 ? sizeof(uint16_t) : sizeof(float);
 }
 
-pba_status check_ready(pba_ctx *c)
+pba_status check_ready(pba_ctx *c, bool may_allocate = true)
 {
     if (c->N == 0) return fail(c, PBA_ESTATE, "no keyframes loaded");
     if (!c->poses_set) return fail(c, PBA_ESTATE, "poses not set");
     if (c->P == 0) return fail(c, PBA_ESTATE, "pairs not set");
     if (!c->queue_ok) {   // a level switch that ran out of memory left none
+        if (!may_allocate) return fail(c, PBA_ESTATE, "the level's work queue is not built");
         HIP_OK(hipSetDevice(c->cfg.device));
         return build_items(c, c->src_h, c->tgt_h);
     }
@@ -1321,7 +1322,7 @@ pba_status pba_evaluate_noalloc(pba_ctx *c, pba_eval_out *out)
 {
     if (!c || !out) return fail(c, PBA_EINVAL, "null argument");
     pba_status s;
-    if ((s = check_ready(c))) return s;
+    if ((s = check_ready(c, false))) return s;
     HIP_OK(hipSetDevice(c->cfg.device));
     // carve the queue counters, per-item partials and per-pair records out of this device's array,
     // each part 256-byte aligned

@@ -207,6 +207,9 @@ def test_level_switch(pba, back, zbuffer):
             with memory_for(0):
                 _refused(pba, ctx.evaluate, pba.PBA_ENOMEM)
                 _refused(pba, lambda: ctx.iterate(1), pba.PBA_ENOMEM)
+            with memory_for(None) as calls:   # it allocates nothing, this neither
+                _refused(pba, lambda: ctx.evaluate(noalloc=True))
+                assert not calls
             ctx.set_level(0)
             if back == "estimate_normals":
                 ctx.estimate_normals()
